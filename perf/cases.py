@@ -28,6 +28,7 @@ import torch
 from paper_2505_09258_amd import binding as L
 
 INIT_STD = 0.3
+NODE_TAG, RELATION_TAG = 0x6E6F6465, 0x72656C73    # of the seeded fill
 LEARNING_RATE = 0.02
 SCORES = {"dot": L.SCORE_DOT, "distmult": L.SCORE_DISTMULT, "complex": L.SCORE_COMPLEX, "transe": L.SCORE_TRANSE_L1}
 LOSSES = {"softmax": L.LOSS_SOFTMAX, "logistic": L.LOSS_LOGISTIC, "softmax_pos": L.LOSS_SOFTMAX_POS, "margin": L.LOSS_MARGIN}
@@ -274,3 +275,74 @@ def tolerance(case):
     if case["score"] == "transe":
         return {"rel": 0.013, "max": 0.99}
     return {"rel": 6e-4, "max": 0.7}
+
+
+def _mix(z):
+    """The output function of splitmix64 on int64 tensors (wrap-around arithmetic, logical shifts)."""
+    z = (z ^ ((z >> 30) & ((1 << 34) - 1))) * (0xBF58476D1CE4E5B9 - (1 << 64))
+    z = (z ^ ((z >> 27) & ((1 << 37) - 1))) * (0x94D049BB133111EB - (1 << 64))
+    return z ^ ((z >> 31) & ((1 << 33) - 1))
+
+
+def _fill(seed, tag, rows, dim):
+    """The seeded initial table of include/legend.h's NULL tables, as float64."""
+    golden = 0x9E3779B97F4A7C15 - (1 << 64)
+    h = torch.tensor([seed], dtype=torch.int64, device="cuda")
+    h = _mix(h + golden + tag)
+    h = _mix(h + golden + torch.arange(rows, device="cuda")[:, None])
+    h = _mix(h + golden + torch.arange(dim, device="cuda")[None, :])
+    u = sum((h >> k) & 0xFFFF for k in (0, 16, 32, 48)) - 131070
+    scale = float(np.float32(float(np.float32(INIT_STD)) * 1.7320508075688772 / 65536.0))
+    return (u.to(torch.float32) * scale).double()
+
+
+def _composed(case, a, r, side):
+    """The row that meets the replaced endpoint: a times the relation, in the score's sense."""
+    if case["score"] == "dot":
+        return a
+    if case["score"] == "transe":
+        return a + r if side == "dst" else a - r
+    if case["score"] == "distmult":
+        return a * r
+    h = case["dim"] // 2
+    ar, ai, rr, ri = a[:, :h], a[:, h:], r[:, :h], r[:, h:]
+    if side == "dst":
+        return torch.cat([ar * rr - ai * ri, ar * ri + ai * rr], 1)
+    return torch.cat([rr * ar + ri * ai, rr * ai - ri * ar], 1)
+
+
+def exact(case, seed):
+    """Scores and ranks of the seeded tables in 64 bits.  Training has none here: two passes of Adagrad from zero states
+    enlarge a rounding to the size that `tolerance` states, so that a distance from 64 bits would say nothing."""
+    if case["kind"] not in ("score", "rank"):
+        return None
+    nodes, m = case["nodes"], case["triples"]
+    rng = np.random.default_rng(seed)
+    src, dst = (torch.from_numpy(rng.integers(0, nodes, m)).cuda() for _ in range(2))
+    E = _fill(seed, NODE_TAG, nodes, case["dim"])
+    r = None
+    if case["relations"]:
+        rel = torch.from_numpy(rng.integers(0, case["relations"], m)).cuda()
+        r = _fill(seed, RELATION_TAG, case["relations"], case["dim"])[rel]
+    cand = torch.from_numpy(rng.integers(0, nodes, case["candidates"])).cuda() if case["candidates"] else None
+
+    def against(q, rows):
+        return -(q - rows).abs().sum(1) if case["score"] == "transe" else (q * rows).sum(1)
+
+    if case["kind"] == "score":
+        return against(_composed(case, E[src], r, "dst"), E[dst]).cpu().numpy()
+    kept, true = (src, dst) if case["sides"] == "dst" else (dst, src)
+    q = _composed(case, E[kept], r, case["sides"])
+    f = against(q, E[true])
+    ids = cand if cand is not None else torch.arange(nodes, device="cuda")
+    greater, equal = (torch.zeros(m, dtype=torch.int64, device="cuda") for _ in range(2))
+    step = 4096 if case["score"] != "transe" else max(1, int(3e7 / (m * case["dim"])))
+    for lo in range(0, ids.numel(), step):
+        part = ids[lo:lo + step]
+        S = -(q[:, None] - E[part]).abs().sum(2) if case["score"] == "transe" else q @ E[part].T
+        other = part[None, :] != true[:, None]
+        greater += ((S > f[:, None]) & other).sum(1)
+        equal += ((S == f[:, None]) & other).sum(1)
+    rank = 1.0 + greater.double() + 0.5 * equal.double()
+    return {"greater": greater.int().cpu().numpy(), "equal": equal.int().cpu().numpy(), "mrr": (1 / rank).mean().item(),
+            **{f"hits{k}": (rank <= k).double().mean().item() for k in (1, 3, 10)}}
