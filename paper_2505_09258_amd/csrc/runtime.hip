@@ -16,6 +16,7 @@
 
 #include "legend_internal.h"
 #include "device_utils.h"
+#include "host_copy.h"
 
 using namespace legend;
 
@@ -123,6 +124,7 @@ struct legend_ctx {
     int64_t edges_cap = 0;
     void* io_dev = nullptr;                 // scratch for score / read calls
     size_t io_cap = 0;
+    HostCopyRing readback;                  // pinned ring of large table reads
     uint32_t prof_mask = 0;
     std::vector<ProfSpan> prof_spans;
     std::vector<hipEvent_t> prof_pool;
@@ -230,6 +232,22 @@ int ensure_io(legend_ctx* c, size_t bytes) {
     return LEGEND_OK;
 }
 
+// Device and host-tier memory into the caller's memory; every stream that could write the parts is idle.  Large reads
+// take the pinned ring (1M x 100 floats: 25 to 38 ms by hipMemcpy), small ones plain copies.
+int read_parts(legend_ctx* c, const std::vector<HostCopyPart>& parts) {
+    size_t total = 0;
+    for (const HostCopyPart& p : parts) total += p.bytes;
+    if (total >= HostCopyRing::kMinBytes && c->readback.prepare()) {
+        HIP_TRY(c, c->readback.run(parts, c->cfg.device, c->copy_out));
+        return LEGEND_OK;
+    }
+    for (const HostCopyPart& p : parts) {
+        if (p.on_device) HIP_TRY(c, hipMemcpy(p.dst, p.src, p.bytes, hipMemcpyDeviceToHost));
+        else std::memcpy(p.dst, p.src, p.bytes);
+    }
+    return LEGEND_OK;
+}
+
 int upload_part_tables(legend_ctx* c) {
     std::vector<float*>& e = c->h_part_emb;
     std::vector<float*>& s = c->h_part_state;
@@ -314,6 +332,7 @@ int do_swap(legend_ctx* c, int evict, int load, bool fence_now, bool early_load 
 void free_ctx(legend_ctx* c) {
     if (!c) return;
     (void)hipSetDevice(c->cfg.device);
+    c->readback.release();                  // every read has waited for its copies
     if (c->compute) (void)hipStreamSynchronize(c->compute);
     if (c->copy) (void)hipStreamSynchronize(c->copy);
     if (c->copy_out) { (void)hipStreamSynchronize(c->copy_out); (void)hipStreamDestroy(c->copy_out); }
@@ -1278,8 +1297,7 @@ int legend_read_embeddings(legend_ctx* c, int32_t table, const int64_t* ids, int
         const float* base = table == LEGEND_TABLE_REL_EMB ? c->E_rel : c->S_rel;
         if (!ids) {
             if (m > c->nrel_rows) return fail(LEGEND_E_RANGE, "m exceeds the relation table");
-            HIP_TRY(c, hipMemcpy(out, base, (size_t)m * rowb, hipMemcpyDeviceToHost));
-            return LEGEND_OK;
+            return read_parts(c, {{reinterpret_cast<char*>(out), reinterpret_cast<const char*>(base), (size_t)m * rowb, true}});
         }
         std::vector<float> all((size_t)c->nrel_rows * d);
         HIP_TRY(c, hipMemcpy(all.data(), base, all.size() * sizeof(float), hipMemcpyDeviceToHost));
@@ -1292,15 +1310,16 @@ int legend_read_embeddings(legend_ctx* c, int32_t table, const int64_t* ids, int
     const size_t off = table == LEGEND_TABLE_NODE_STATE ? (size_t)c->Rp * d : 0;
     if (!ids) {
         if (m > c->V) return fail(LEGEND_E_RANGE, "m exceeds num_nodes");
+        std::vector<HostCopyPart> parts;
         for (int p = 0; p < c->n; ++p) {
             int64_t lo = (int64_t)p * c->Rp;
             if (lo >= m) break;
             int64_t rows = std::min<int64_t>(c->Rp, m - lo);
             int sl = c->part_slot[p];
-            if (sl >= 0) HIP_TRY(c, hipMemcpy(out + lo * d, c->slot_mem[sl] + off, (size_t)rows * rowb, hipMemcpyDeviceToHost));
-            else std::memcpy(out + lo * d, c->host_part[p] + off, (size_t)rows * rowb);
+            const float* from = (sl >= 0 ? c->slot_mem[sl] : c->host_part[p]) + off;
+            parts.push_back({reinterpret_cast<char*>(out + lo * d), reinterpret_cast<const char*>(from), (size_t)rows * rowb, sl >= 0});
         }
-        return LEGEND_OK;
+        return read_parts(c, parts);
     }
     for (int64_t k = 0; k < m; ++k)
         if (ids[k] < 0 || ids[k] >= c->V) return fail(LEGEND_E_RANGE, "node id %lld out of range", (long long)ids[k]);

@@ -1,0 +1,25 @@
+"""Large table reads (pinned ring, several threads) against the table that went in, bit for bit."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+# 4 MB is the smallest read that takes the ring, 24 MB one full ring of 2 MB blocks
+@pytest.mark.parametrize("V,d,n,capacity", [(8_191, 128, 1, 1), (8_192, 128, 1, 1), (98_304, 64, 1, 1), (98_305, 64, 3, 3),
+                                            (400_003, 50, 5, 3)])
+def test_whole_table_read_returns_the_table(V, d, n, capacity):
+    from paper_2505_09258_amd import binding as L
+    node = np.random.default_rng(V).standard_normal((V, d)).astype(np.float32)
+    cfg = L.make_config(num_nodes=V, dim=d, num_partitions=n, buffer_capacity=capacity, batch_size=100, chunk_size=10,
+                        num_negs=10, seed=1)
+    ctx = L.legend_init_partitions(cfg, node, None)
+    try:
+        for p in range(capacity):
+            L.legend_swap_partition(ctx, -1, p)                # the others are read from the host tier
+        for m in (V, V - 1):
+            assert (L.legend_read_embeddings(ctx, L.TABLE_NODE_EMB, None, m, d) == node[:m]).all()
+        assert not L.legend_read_embeddings(ctx, L.TABLE_NODE_STATE, None, V, d).any()
+    finally:
+        L.legend_destroy(ctx)
