@@ -75,6 +75,46 @@ def test_exact_counts_on_integer_embeddings(score, d, side):
         L.legend_destroy(ctx)
 
 
+@pytest.mark.parametrize("d,m,n_cand", [(1, 1, 1), (31, 63, 127), (32, 64, 128), (33, 127, 129), (48, 128, 255),
+                                        (66, 129, 257), (100, 192, 640), (512, 65, 385)])
+def test_exact_counts_at_tile_edges(d, m, n_cand):
+    """One less, one more and exactly a tile of triples, of candidates and of the components of one step."""
+    rng = np.random.default_rng(d)
+    V = 700
+    node = rng.integers(-2, 3, size=(V, d)).astype(np.float32)
+    L, ctx = _ctx(V, d, 2, model.DOT, node, None, 0)
+    try:
+        for p in range(2):
+            L.legend_swap_partition(ctx, -1, p)
+        src, _, dst = _triples(rng, V, 0, m)
+        cand = rng.integers(0, V, n_cand)
+        g, q, _ = L.legend_rank_edges(ctx, src, None, dst, DST, cand)
+        wg, wq = rank.rank_counts(model.DOT, node, None, src, None, dst, DST, cand)
+        assert (g == wg).all() and (q == wq).all()
+    finally:
+        L.legend_destroy(ctx)
+
+
+def test_infinite_scores_count_as_the_plain_sums_say():
+    """An infinite component makes a score +inf (counted), -inf or NaN (not counted): integers elsewhere, so exact."""
+    rng = np.random.default_rng(5)
+    V, d = 300, 40
+    node = rng.integers(1, 4, size=(V, d)).astype(np.float32)
+    node[7, 3], node[8, 3] = np.inf, -np.inf
+    node[9, :2] = np.inf, -np.inf                              # inf - inf
+    L, ctx = _ctx(V, d, 1, model.DOT, node, None, 0)
+    try:
+        L.legend_swap_partition(ctx, -1, 0)
+        src, dst = rng.integers(20, V, 70), rng.integers(20, V, 70)
+        g, q, _ = L.legend_rank_edges(ctx, src, None, dst, DST, None)
+        S = node[src].astype(np.float64) @ np.delete(node, [7, 8, 9], axis=0).astype(np.float64).T
+        f = (node[src].astype(np.float64) * node[dst]).sum(1)
+        assert (g == (S > f[:, None]).sum(1) + 1).all()        # and the one candidate whose score is +inf
+        assert (q == (S == f[:, None]).sum(1) - 1).all()       # without the true endpoint
+    finally:
+        L.legend_destroy(ctx)
+
+
 def _band(score, node, rel, src, r, dst, side):
     """fp32 error bound of a d-term dot product, norm-wise: 1e-5 * |q| * max|c| (the bar of the score parity)."""
     E = node.astype(np.float64)
