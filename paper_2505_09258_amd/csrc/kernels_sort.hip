@@ -30,6 +30,19 @@ hipError_t launch_prepare(hipStream_t st, const BatchGeom& g, const BucketParams
     return hipGetLastError();
 }
 
+// The same for a group of small batches, batch blockIdx.y of it into its own slab.
+__global__ void __launch_bounds__(256)
+k_prepare_group(BatchGeom g, BucketParams bp, uint64_t hash, int64_t batch0, uint32_t* __restrict__ slabs) {
+    const int64_t b = batch0 + blockIdx.y, B = g.P;
+    const int64_t rest = bp.m - b * B;
+    if (rest < B) set_positives(g, (int)rest);
+    bp.batch_lo = b * B;
+    bp.hash_prefix = hash_fold(hash, (uint64_t)b);
+    uint32_t* slab = slabs + blockIdx.y * SmallSlab::words;
+    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (o < g.n_occ) slab[SmallSlab::keys + o] = occurrence_key(g, bp, o, reinterpret_cast<int32_t*>(slab + SmallSlab::neg_ids));
+}
+
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;   // keys per block
@@ -271,6 +284,9 @@ static hipError_t launch_segments(hipStream_t st, int64_t n, const uint32_t* sor
 // latency-bound tiny batch pays one launch instead of some twenty.  (Making the keys in this kernel
 // as well was tried: one workgroup walking a few thousand occurrences, each with its 64-bit index
 // arithmetic and hashes, took longer than the launch it saved: 89 against 54 us per c1 batch.)
+// It sorts on one compute unit and takes as long for one batch as for one batch on each of many units: a bucket of small
+// batches has the index sides of up to kSmallGroup of them made by one launch (stride: words from one batch's buffers to the
+// next one's).
 // Same stable ranking as the multi-block scatter: wave w of the sixteen owns a contiguous share of the keys.
 // ------------------------------------------------------------------------------------------
 
@@ -278,12 +294,16 @@ constexpr int kSmallThreads = 1024;
 static_assert(kSmallThreads >= kRadix && kSmallSortMax % kSmallThreads == 0, "small sort geometry");
 
 __global__ void __launch_bounds__(kSmallThreads)
-k_small_sort_segments(const uint32_t* __restrict__ keys_in, int n, int passes, uint32_t* __restrict__ vals_out,
+k_small_sort_segments(const uint32_t* __restrict__ keys_in, int n, int n_last, int64_t stride, int passes, uint32_t* __restrict__ vals_out,
                       uint32_t* __restrict__ uniq_keys, uint32_t* __restrict__ seg_start,
                       uint32_t* __restrict__ counters, unsigned long long* __restrict__ uniq_total,
                       uint32_t* __restrict__ long_list, uint32_t* __restrict__ unit_start, int plan_long) {
     constexpr int kWaves = kSmallThreads / kWave;
     extern __shared__ uint32_t sm[];
+    if (blockIdx.x == gridDim.x - 1) n = n_last;
+    const int64_t shift_words = (int64_t)blockIdx.x * stride;
+    keys_in += shift_words; vals_out += shift_words; uniq_keys += shift_words; seg_start += shift_words;
+    counters += shift_words; long_list += shift_words; unit_start += shift_words;
     auto kb = [&](int b) { return sm + b * kSmallSortMax; };                     // key buffers 0 / 1
     auto vb = [&](int b) { return sm + (2 + b) * kSmallSortMax; };               // value buffers 0 / 1
     uint32_t* cnt = sm + 4 * kSmallSortMax;            // [kWaves][256]
@@ -394,7 +414,7 @@ k_small_sort_segments(const uint32_t* __restrict__ keys_in, int n, int passes, u
     if (tid == 0) {
         seg_start[total] = (uint32_t)n;
         counters[0] = total;
-        *uniq_total += total;
+        atomicAdd(uniq_total, (unsigned long long)total);
         wsum[kWaves + 1] = 0;                 // long rows
         wsum[kWaves + 2] = 0;                 // their units
     }
@@ -440,27 +460,49 @@ k_small_sort_segments(const uint32_t* __restrict__ keys_in, int n, int passes, u
     }
 }
 
+static hipError_t launch_small_sort(hipStream_t st, int count, int64_t n, int64_t n_last, int64_t stride, int key_bits,
+                                    const uint32_t* keys, uint32_t* vals, uint32_t* uniq_keys, uint32_t* seg_start, uint32_t* counters,
+                                    unsigned long long* uniq_total, uint32_t* long_list, uint32_t* unit_start, bool plan_long) {
+    int passes = (key_bits + 7) / 8;
+    if (passes < 1) passes = 1;
+    const size_t lds = (4 * (size_t)kSmallSortMax + 2 * (kSmallThreads / kWave) * kRadix + (kSmallThreads / kWave) + 8) * sizeof(uint32_t);
+    static PerDeviceFlag attr_set;
+    if (attr_set.pending()) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_small_sort_segments),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        attr_set.set();
+    }
+    hipLaunchKernelGGL(k_small_sort_segments, dim3((unsigned)count), dim3(kSmallThreads), lds, st, keys, (int)n, (int)n_last, stride,
+                       passes, vals, uniq_keys, seg_start, counters, uniq_total, long_list, unit_start, plan_long ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_small_group(hipStream_t st, const BatchGeom& full, const BucketParams& bp, uint64_t hash, int64_t batch0,
+                              int count, int key_bits, uint32_t* slabs, unsigned long long* uniq_total, bool plan_long) {
+    if (count < 1 || count > kSmallGroup || full.n_occ < 1 || full.n_occ > kSmallSortMax) return hipErrorInvalidValue;
+    BatchGeom last = full;
+    const int64_t rest = bp.m - (batch0 + count - 1) * (int64_t)full.P;
+    if (rest < 1) return hipErrorInvalidValue;
+    if (rest < full.P) set_positives(last, (int)rest);
+    hipLaunchKernelGGL(k_prepare_group, dim3((unsigned)((full.n_occ + 255) / 256), (unsigned)count), dim3(256), 0, st, full, bp, hash,
+                       batch0, slabs);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    using S = SmallSlab;
+    return launch_small_sort(st, count, full.n_occ, last.n_occ, S::words, key_bits, slabs + S::keys, slabs + S::vals, slabs + S::uniq_keys,
+                             slabs + S::seg_start, slabs + S::counters, uniq_total, slabs + S::long_list, slabs + S::unit_start, plan_long);
+}
+
 hipError_t launch_sort_and_segments(hipStream_t st, const BatchGeom& g, const BucketParams& bp, int key_bits,
                                     const Workspace& ws, int* out_buf, bool plan_long) {
     *out_buf = 0;
     const int64_t n = g.n_occ;
     if (n <= 0) return hipSuccess;
-    int passes = (key_bits + 7) / 8;
-    if (passes < 1) passes = 1;
     if (n <= kSmallSortMax) {
-        const size_t lds = (4 * (size_t)kSmallSortMax + 2 * (kSmallThreads / kWave) * kRadix + (kSmallThreads / kWave) + 8) * sizeof(uint32_t);
-        static PerDeviceFlag attr_set;
-        if (attr_set.pending()) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_small_sort_segments),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            attr_set.set();
-        }
-        hipLaunchKernelGGL(k_small_sort_segments, dim3(1), dim3(kSmallThreads), lds, st, ws.keys[0], (int)n, passes,
-                           ws.vals[1], ws.uniq_keys, ws.seg_start, ws.counters, ws.uniq_total, ws.long_list,
-                           ws.unit_start, plan_long ? 1 : 0);
         *out_buf = 1;
-        return hipGetLastError();
+        return launch_small_sort(st, 1, n, n, 0, key_bits, ws.keys[0], ws.vals[1], ws.uniq_keys, ws.seg_start, ws.counters,
+                                 ws.uniq_total, ws.long_list, ws.unit_start, plan_long);
     }
     hipError_t e = launch_sort(st, n, key_bits, ws, out_buf);
     if (e != hipSuccess) return e;

@@ -48,6 +48,24 @@ struct BatchGeom {
     int64_t n_occ;        // total occurrences
 };
 
+// the fields that follow from the number of positives
+__host__ __device__ inline void set_positives(BatchGeom& g, int P) {
+    g.P = P;
+    g.nchunks = (P + g.C - 1) / g.C;
+    g.per_side = (int64_t)g.roles * P + (int64_t)g.nchunks * g.T * g.N;
+    g.n_occ = g.per_side * g.sides;
+}
+
+// Index sides of several small batches (every batch at most kSmallSortMax gradient rows) side by side: one slab of
+// 32-bit words per batch.
+constexpr int kSmallGroup = 32;
+struct SmallSlab {
+    static constexpr int64_t neg_ids = 0, keys = neg_ids + kSmallSortMax, vals = keys + kSmallSortMax, uniq_keys = vals + kSmallSortMax,
+                             seg_start = uniq_keys + kSmallSortMax, long_list = seg_start + kSmallSortMax + 8, unit_start = long_list + 128,
+                             counters = unit_start + 136, words = counters + 8;
+};
+static_assert(kSmallSortMax / (kLongLen + 1) + 2 <= 128, "long rows of a small batch");
+
 // Everything the per-batch kernels need to know about the bucket and the model.
 struct BucketParams {
     const int32_t* edges;      // device, [m][3]
@@ -130,6 +148,10 @@ hipError_t launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t v, int64_t n);
 // indices end up in ws.vals[*out_buf].  Batches of at most kSmallSortMax gradient rows do all of it in
 // the one launch of launch_sort_and_segments.
 hipError_t launch_prepare(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws);
+// small batches batch0 .. batch0 + count - 1 of a bucket, B positives each (the bucket's last one fewer), into consecutive
+// slabs; hash: the hash state before the batch number.  Sorted occurrence indices at SmallSlab::vals.
+hipError_t launch_small_group(hipStream_t st, const BatchGeom& full, const BucketParams& bp, uint64_t hash, int64_t batch0,
+                              int count, int key_bits, uint32_t* slabs, unsigned long long* uniq_total, bool plan_long);
 hipError_t launch_sort_and_segments(hipStream_t st, const BatchGeom& g, const BucketParams& bp, int key_bits,
                                     const Workspace& ws, int* out_buf, bool plan_long);
 // long rows and their units from the segment bounds; nothing to do for n_occ <= kSmallSortMax

@@ -119,6 +119,7 @@ struct legend_ctx {
     Workspace ws{};                         // even batches of a call; also every serial path
     Workspace ws_alt[2]{};                  // batches 1 and 2 (mod 3): own index-side buffers, the rest shared with ws
     BatchGeom gmax{};
+    uint32_t* small_slabs = nullptr;        // two sets of kSmallGroup slabs where a full batch is small, else null
     int key_bits = 0;
     int32_t* edges_dev = nullptr;
     int64_t edges_cap = 0;
@@ -159,18 +160,15 @@ int64_t rows_valid(const legend_ctx* c, int part) {
 BatchGeom make_geom(const legend_ctx* c, int P) {
     BatchGeom g{};
     const legend_config& cf = c->cfg;
-    g.P = P;
     g.C = cf.chunk_size;
     g.N = cf.num_negs;
     g.T = row_tiles_for(cf.chunk_size, c->d);
     g.rows_tile = rows_per_tile_for(cf.chunk_size, c->d);
-    g.nchunks = (P + g.C - 1) / g.C;
     g.sides = cf.corrupt == LEGEND_CORRUPT_BOTH ? 2 : 1;
     g.side_id[0] = cf.corrupt == LEGEND_CORRUPT_SRC ? 1 : 0;
     g.side_id[1] = 1;
     g.roles = c->uses_rel ? 3 : 2;
-    g.per_side = (int64_t)g.roles * P + (int64_t)g.nchunks * g.T * g.N;
-    g.n_occ = g.per_side * g.sides;
+    set_positives(g, P);
     return g;
 }
 
@@ -347,7 +345,7 @@ void free_ctx(legend_ctx* c) {
     void* frees[] = {c->E_rel, c->S_rel, c->d_part_emb, c->d_part_state, c->ws.neg_ids, c->ws.keys[0], c->ws.keys[1],
                      c->ws.vals[0], c->ws.vals[1], c->ws.ghist, c->ws.scan_tmp, c->ws.uniq_keys, c->ws.seg_start,
                      c->ws.counters, c->ws.long_list, c->ws.unit_start, c->ws.long_partial, c->ws.uniq_total, c->ws.grad, c->ws.loss_partial, c->ws.redo, c->ws.redo_total, c->ws.loss_sum, c->ws.gemm_Q, c->ws.gemm_G, c->ws.gemm_f,
-                     c->ws.gemm_a, c->ws.gemm_S, c->edges_dev,
+                     c->ws.gemm_a, c->ws.gemm_S, c->edges_dev, c->small_slabs,
                      c->io_dev};
     for (void* p : frees) if (p) (void)hipFree(p);
     for (Workspace& o : c->ws_alt) {
@@ -463,13 +461,14 @@ int bucket_params(legend_ctx* c, int i, int j, const int32_t* dev_edges, int64_t
     return LEGEND_OK;
 }
 
-uint64_t batch_hash_prefix(const legend_ctx* c, int epoch, int i, int j, int64_t b) {
+uint64_t bucket_hash_prefix(const legend_ctx* c, int epoch, int i, int j) {
     uint64_t h = c->cfg.seed;
     h = hash_fold(h, (uint64_t)(int64_t)epoch);
     h = hash_fold(h, (uint64_t)i);
-    h = hash_fold(h, (uint64_t)j);
-    h = hash_fold(h, (uint64_t)b);
-    return h;
+    return hash_fold(h, (uint64_t)j);
+}
+uint64_t batch_hash_prefix(const legend_ctx* c, int epoch, int i, int j, int64_t b) {
+    return hash_fold(bucket_hash_prefix(c, epoch, i, j), (uint64_t)b);
 }
 
 // index side of one batch: negatives, keys, sort, segment heads, all on stream `st` into `ws`
@@ -675,6 +674,7 @@ int legend_init_partitions(const legend_config* cfg, const float* init_node_emb,
     Workspace& w = c->ws;
     w.cap_occ = occ;
     w.cap_wg = nwg;
+    if (occ <= kSmallSortMax) INIT_RC(dev_alloc(c, &c->small_slabs, (size_t)2 * kSmallGroup * SmallSlab::words));
     INIT_RC(dev_alloc(c, &w.neg_ids, (size_t)c->gmax.sides * c->gmax.nchunks * c->gmax.N));
     for (int k = 0; k < 2; ++k) {
         INIT_RC(dev_alloc(c, &w.keys[k], (size_t)occ));
@@ -850,7 +850,40 @@ int legend_train_bucket_range(legend_ctx* c, int32_t i, int32_t j, const int32_t
     int sorted_of[3] = {0, 0, 0};
     auto wset = [&](int k) -> const Workspace& { return k == 0 ? c->ws : c->ws_alt[k - 1]; };
     const bool ahead = !c->serial_sort;
-    if (ahead && batch_begin < batch_end) {
+    // Small batches: the index sides of a whole group of them are made by two launches, the first group's on the compute stream
+    // (a call of one batch crosses to no other stream), the next group's beside the current one.  A small batch then is its
+    // chunk and update kernels, one after the other; with an index side of its own for every batch it also waited
+    // for two events, which took longer than either kernel (tiny configuration: 36 -> 26 us a batch).
+    const bool grouped = ahead && c->small_slabs != nullptr;
+    auto enqueue_group = [&](hipStream_t st, int64_t first, int set) -> int {
+        ProfScope ps(c, KC_SORT, st);
+        HIP_TRY(c, launch_small_group(st, c->gmax, bp, bucket_hash_prefix(c, epoch, i, j), first,
+                                      (int)std::min<int64_t>(kSmallGroup, batch_end - first), c->key_bits,
+                                      c->small_slabs + (size_t)set * kSmallGroup * SmallSlab::words, c->ws.uniq_total,
+                                      c->cfg.update_mode != LEGEND_UPDATE_ATOMIC));
+        return LEGEND_OK;
+    };
+    auto small_workspace = [&](int set, int64_t k) {
+        uint32_t* slab = c->small_slabs + ((size_t)set * kSmallGroup + k) * SmallSlab::words;
+        Workspace w = c->ws;
+        w.neg_ids = reinterpret_cast<int32_t*>(slab + SmallSlab::neg_ids);
+        w.keys[0] = w.keys[1] = slab + SmallSlab::keys;
+        w.vals[0] = w.vals[1] = slab + SmallSlab::vals;
+        w.uniq_keys = slab + SmallSlab::uniq_keys;
+        w.seg_start = slab + SmallSlab::seg_start;
+        w.counters = slab + SmallSlab::counters;
+        w.long_list = slab + SmallSlab::long_list;
+        w.unit_start = slab + SmallSlab::unit_start;
+        return w;
+    };
+    if (grouped && batch_begin < batch_end) {
+        if (nb > kSmallGroup) {
+            HIP_TRY(c, hipEventRecord(c->ev_start, c->compute));    // edges staged, earlier calls done with the slabs
+            HIP_TRY(c, hipStreamWaitEvent(c->aux, c->ev_start, 0));
+        }
+        rc = enqueue_group(c->compute, batch_begin, 0);
+        if (rc) return rc;
+    } else if (ahead && batch_begin < batch_end) {
         BatchGeom g0;
         batch_params(batch_begin, &g0);
         HIP_TRY(c, hipEventRecord(c->ev_start, c->compute));        // edges staged, earlier calls done with the workspaces
@@ -860,12 +893,24 @@ int legend_train_bucket_range(legend_ctx* c, int32_t i, int32_t j, const int32_t
         HIP_TRY(c, hipEventRecord(c->ev_index[0], c->aux));
     }
     for (int64_t b = batch_begin; b < batch_end; ++b) {
-        const int cur = ahead ? (int)((b - batch_begin) % 3) : 0;
-        const Workspace& ws = wset(cur);
+        const int64_t in_group = (b - batch_begin) % kSmallGroup;
+        const int group_set = (int)((b - batch_begin) / kSmallGroup % 2);
+        const int cur = ahead && !grouped ? (int)((b - batch_begin) % 3) : 0;
+        const Workspace small_ws = grouped ? small_workspace(group_set, in_group) : Workspace{};
+        const Workspace& ws = grouped ? small_ws : wset(cur);
         BatchGeom g;
         batch_params(b, &g);
         edges_done += g.P;
-        if (ahead) {
+        if (grouped) {
+            if (in_group == 0 && b > batch_begin) HIP_TRY(c, hipStreamWaitEvent(c->compute, c->ev_index[group_set], 0));
+            if (in_group == 0 && b + kSmallGroup < batch_end) {
+                // the next group's slabs are free once the last update of the group before this one is done
+                if (b > batch_begin) HIP_TRY(c, hipStreamWaitEvent(c->aux, c->ev_updated[group_set ^ 1], 0));
+                rc = enqueue_group(c->aux, b + kSmallGroup, group_set ^ 1);
+                if (rc) return rc;
+                HIP_TRY(c, hipEventRecord(c->ev_index[group_set ^ 1], c->aux));
+            }
+        } else if (ahead) {
             HIP_TRY(c, hipStreamWaitEvent(c->compute, c->ev_index[cur], 0));
         } else {
             rc = enqueue_index_side(c, c->compute, g, bp, ws, &sorted_of[0]);
@@ -894,7 +939,7 @@ int legend_train_bucket_range(legend_ctx* c, int32_t i, int32_t j, const int32_t
             HIP_TRY(c, launch_loss_reduce(c->compute, loss_terms, ws));
         }
         if (aside) HIP_TRY(c, hipEventRecord(c->ev_chunk_done, c->compute));
-        if (ahead && b + 1 < batch_end) {
+        if (ahead && !grouped && b + 1 < batch_end) {
             // next batch's index side: its buffers are free once the update of batch b-2 is done
             const int nxt = (cur + 1) % 3;
             BatchGeom gn;
@@ -933,7 +978,11 @@ int legend_train_bucket_range(legend_ctx* c, int32_t i, int32_t j, const int32_t
             }
             if (aside) HIP_TRY(c, hipStreamWaitEvent(c->compute, c->ev_long_done, 0));
         }
-        if (ahead) HIP_TRY(c, hipEventRecord(c->ev_updated[cur], c->compute));
+        if (grouped) {
+            if (in_group == kSmallGroup - 1) HIP_TRY(c, hipEventRecord(c->ev_updated[group_set], c->compute));
+        } else if (ahead) {
+            HIP_TRY(c, hipEventRecord(c->ev_updated[cur], c->compute));
+        }
         c->batches_done += 1;
     }
     if (stats) HIP_TRY(c, hipEventRecord(c->ev_t1, c->compute));

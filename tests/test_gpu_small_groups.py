@@ -1,0 +1,43 @@
+"""Small batches, whose index sides are made in groups of 32 on two sets of buffers, against the same calls with every
+batch's index side made on its own (LEGEND_SERIAL_SORT=1): same sums in the same order, so the same bits."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(monkeypatch, serial, calls, m, update_mode=0):
+    from paper_2505_09258_amd import binding as L
+    V, d, B = 900, 20, 60
+    rng = np.random.default_rng(3)
+    node = (0.3 * rng.standard_normal((V, d))).astype(np.float32)
+    rel = (0.3 * rng.standard_normal((4, d))).astype(np.float32)
+    edges = np.stack([(V // 2 * rng.random(m) ** 3), rng.integers(0, 4, m), V // 2 * rng.random(m)], 1).astype(np.int32)
+    monkeypatch.setenv("LEGEND_SERIAL_SORT", "1" if serial else "0")
+    cfg = L.make_config(num_nodes=V, dim=d, num_partitions=2, num_relations=4, score=L.SCORE_DISTMULT, corrupt=L.CORRUPT_BOTH,
+                        batch_size=B, chunk_size=20, num_negs=33, num_degree_negs=5, seed=2)
+    ctx = L.legend_init_partitions(cfg, node, rel)
+    try:
+        for p in range(2):
+            L.legend_swap_partition(ctx, -1, p)
+        out = []
+        for k, (lo, hi) in enumerate(calls):
+            st = L.legend_train_bucket_range(ctx, 0, 1, edges, epoch=k, batch_begin=lo, batch_end=hi)
+            out.append(st["loss_sum"])
+        out.append(L.legend_unique_rows_read(ctx))
+        return out, [L.legend_read_embeddings(ctx, t, None, V if t < 2 else 4, d) for t in range(4)]
+    finally:
+        L.legend_destroy(ctx)
+
+
+# whole buckets of 1, 31, 32, 33, 64, 65 and 97 batches with a ragged last one, and ranges that begin and end inside
+@pytest.mark.parametrize("m,calls", [(59, [(0, 1)]), (31 * 60 - 1, [(0, 31)]), (32 * 60, [(0, 32)] * 2), (33 * 60 - 59, [(0, 33)] * 2),
+                                     (64 * 60, [(0, 64)]), (65 * 60 - 7, [(0, 65)] * 2), (97 * 60 - 30, [(0, 97)] * 3),
+                                     (80 * 60 - 11, [(3, 40), (40, 41), (10, 80)])])
+def test_groups_give_the_bits_of_single_batches(monkeypatch, m, calls):
+    a, ta = _run(monkeypatch, False, calls, m)
+    b, tb = _run(monkeypatch, True, calls, m)
+    assert a == b
+    for x, y in zip(ta, tb):
+        assert (x == y).all()
