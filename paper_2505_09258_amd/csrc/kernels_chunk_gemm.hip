@@ -1,36 +1,83 @@
 // Batch computation for wide embeddings (128 < dim <= 512; paper Sec. 2.1
-// stage 5, Sec. 6) as a short chain of tiled fp32-MFMA contractions.  A (row tile of <= 112
+// stage 5, Sec. 6) as a short chain of tiled contractions.  A (row tile of <= 112
 // positives) x (all N negatives) score block does not fit on chip next to d-wide operand tiles,
 // so the scores go through a device buffer that stays in the L2 / Infinity cache (the paper keeps
 // its "Intermediate Result 3" in global memory for the same reason):
 //   k_gemm_compose   Q = theta_s (x) theta_r (or conj(theta_r) (x) theta_d), positive scores f
-//   k_gemm_scores    S = Q Neg^T, 112 x 64 tiles, the dimension streamed in slices of 80 columns
+//   k_gemm_scores    S = Q Neg^T, 112 x 128 tiles
 //   k_gemm_rowstats  per row: log-sum-exp, loss term, dL/df; S is replaced by the weights W = dL/dS
 //   k_gemm_gq        G_Q = W Neg
 //   k_gemm_gneg      G_neg = W^T Q, written to the gradient rows of the negatives
 //   k_gemm_chain     chain rule: gradient rows of theta_s, theta_r, theta_d of the positives
-// All contractions use 16x16x4 MFMA with the contraction index in groups of 16 (lane group g
-// supplies k = 16G + 4g + s to four consecutive MFMAs), so a k-contiguous operand is one 128-bit
-// LDS read per four MFMAs; operands whose contraction index is the slow one are read 32 bits at
-// a time.
+// The contractions were bound by the fp32 matrix pipe and the LDS reads that feed it (58 to 75 TFLOP/s of 139).  Now every
+// operand is cut into three bf16 parts on its way into LDS, as fp32 products of six bf16 instructions (split_bf16.h), and
+// read back as the eight contraction elements of a lane, one 128-bit read per part.  All three work on slices of 32
+// contraction elements with 128 columns or negatives to a tile, the next slice on its way from memory; about 50 KB of
+// LDS and at most 168 registers leave three workgroups to a compute unit, which cut and multiply in turn.  An operand whose contraction
+// index is the slow one in memory is loaded by one thread per column, eight rows each: whole lines per instruction.
+// Measured on batches of 10 000 edges, both sides, 1000 negatives, d = 400 (200 row tiles of 100): G_Q 276 -> 161 us, G_neg 255 ->
+// 178 us, an epoch of 49 batches with its read 52.0 -> 39.4 ms.  What bounds them now: vector instructions of the cutting
+// and matrix instructions take about a fifth of the time each, the rest waits for slices gathered from the tables.  Below
+// d = 128 the chain loses to the two-sweep kernel (d = 50, 50 000 edges a batch: 14.1 against 12.7 ms an epoch), also with
+// the scores taken in turns that stay in the Infinity cache.
 #include "chunk_common.h"
+#include "split_bf16.h"
 
 namespace legend {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ inline f32x4 mfma16g(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 constexpr int kGRows = 112;              // rows of a tile of positives: seven 16-row blocks
-constexpr int kGRowBlocks = kGRows / 16;
-constexpr int kGNeg = 64;                // negatives per tile
-constexpr int kGSlice = 80;              // columns of the dimension per slice: five 16-column blocks
-constexpr int kGSS = kGSlice + 4;        // LDS row stride of a slice
-constexpr int kGWS = kGNeg + 4;          // LDS row stride of a W tile
+constexpr int kGNeg = 64;                // negatives per tile of the score buffer
+constexpr int kGTile = 128;              // negatives or columns per workgroup
+constexpr int kGK = 32;                  // contraction elements per slice
+constexpr int kGThreads = 256;
 
 static_assert(kGRows == kWideRowTile, "tile geometry");
+
+// Elements k..k+7 of a row of d; elements past its end are others of the row (loads only: what is done to a loaded value
+// at once waits for it).
+template <bool VEC>                           // rows are 16-byte aligned (d a multiple of four)
+__device__ inline void load8(const float* __restrict__ row, int k, int d, float (&v)[8]) {
+    if (VEC) {
+        const float4 a = *reinterpret_cast<const float4*>(row + (k < d ? k : 0));
+        const float4 b = *reinterpret_cast<const float4*>(row + (k + 4 < d ? k + 4 : 0));
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = row[min(k + t, d - 1)];
+    }
+}
+// zero where element k + t does not exist
+__device__ inline void zero_past(float (&v)[8], int k, int n) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+        if (k + t >= n) v[t] = 0.f;
+}
+
+// acc[a][b] += A_a B_b^T of one slice for RA blocks of 16 rows (of which two at a time are in registers) and two blocks
+// of 16 columns
+template <int RA, class TA, class TB>
+__device__ __forceinline__ void slice_mfma(const char* As, const char* Bs, int col0, int l15, int gq, f32v4 (&acc)[RA][2]) {
+    Split8 B[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) B[b] = TB::load(Bs, col0 + 16 * b + l15, gq);
+#pragma unroll
+    for (int a = 0; a + 1 < RA; a += 2) {
+        Split8 A[2];
+        A[0] = TA::load(As, 16 * a + l15, gq);
+        A[1] = TA::load(As, 16 * a + 16 + l15, gq);
+        f32v4 c[2][2] = {{acc[a][0], acc[a][1]}, {acc[a + 1][0], acc[a + 1][1]}};
+        split_mfma(A, B, c);
+        acc[a][0] = c[0][0]; acc[a][1] = c[0][1];
+        acc[a + 1][0] = c[1][0]; acc[a + 1][1] = c[1][1];
+    }
+    if constexpr (RA % 2 == 1) {
+        Split8 A[1] = {TA::load(As, 16 * (RA - 1) + l15, gq)};
+        f32v4 c[1][2] = {{acc[RA - 1][0], acc[RA - 1][1]}};
+        split_mfma(A, B, c);
+        acc[RA - 1][0] = c[0][0]; acc[RA - 1][1] = c[0][1];
+    }
+}
 
 // Workgroup ids are dealt round-robin to the eight XCDs, each with its own L2.  The tiled
 // kernels launch a one-dimensional grid of 8 * ceil(total / 8) workgroups and turn the hardware
@@ -113,151 +160,90 @@ k_gemm_compose(BatchGeom g, BucketParams bp, float* __restrict__ Q, float* __res
     if (threadIdx.x == 0) fpos[idx] = red[0];
 }
 
-// A thread's share of a [rows][64] tile of W (from the buffer the row statistics left) and of a
-// [64][80] tile of negatives, fetched into registers one tile ahead of their use.
-template <int THREADS>
-struct WTileRegs {
-    static constexpr int V4 = kGNeg / 4;
-    static constexpr int ITEMS = (kGRows * V4 + THREADS - 1) / THREADS;
-    float4 v[ITEMS];
-    // Wtile: start of the row tile's block; the 64-negative tile n0 / 64 is the contiguous piece [rows_tile][64]
-    __device__ void fetch(const float* Wtile, int rows_tile, int nrows, int n0, int tid) {
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            const int idx = tid + THREADS * k;
-            const int row = idx / V4, c4 = idx - row * V4;
-            v[k] = row < nrows ? *reinterpret_cast<const float4*>(Wtile + ((int64_t)(n0 / kGNeg) * rows_tile + row) * kGNeg + 4 * c4)
-                               : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    }
-    __device__ void store(float* Wt, int tid) const {
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            const int idx = tid + THREADS * k;
-            const int row = idx / V4, c4 = idx - row * V4;
-            if (row < kGRows) *reinterpret_cast<float4*>(Wt + row * kGWS + 4 * c4) = v[k];
-        }
-    }
-};
-
-template <int THREADS, int ROWS, int WIDTH = kGSlice>
-struct SliceRegs {                            // [ROWS][WIDTH columns] of row-major fp32 rows, LDS row stride WIDTH + 4
-    static constexpr int V4 = WIDTH / 4;
-    static constexpr int ITEMS = (ROWS * V4 + THREADS - 1) / THREADS;
-    float4 v[ITEMS];
-    // row_ptr(row) gives the start of the row or nullptr for a row that does not exist
-    template <class F>
-    __device__ void fetch(F&& row_ptr, int c0, int d, int tid) {
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            const int idx = tid + THREADS * k;
-            const int row = idx / V4, c4 = idx - row * V4;
-            const float* p = row < ROWS ? row_ptr(row) : nullptr;
-            const int c = c0 + 4 * c4;
-            float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (p && c < d) {
-                if ((d & 3) == 0) {           // rows are 16-byte aligned only then
-                    o = *reinterpret_cast<const float4*>(p + c);
-                } else if ((d & 1) == 0) {    // 8-byte aligned rows: two 64-bit loads
-                    const float2 a = *reinterpret_cast<const float2*>(p + c);
-                    o.x = a.x; o.y = a.y;
-                    if (c + 2 < d) {
-                        const float2 b = *reinterpret_cast<const float2*>(p + c + 2);
-                        o.z = b.x; o.w = b.y;
-                    }
-                } else {
-                    o.x = p[c];
-                    if (c + 1 < d) o.y = p[c + 1];
-                    if (c + 2 < d) o.z = p[c + 2];
-                    if (c + 3 < d) o.w = p[c + 3];
-                }
-            }
-            v[k] = o;
-        }
-    }
-    __device__ void store(float* T, int tid) const {
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            const int idx = tid + THREADS * k;
-            const int row = idx / V4, c4 = idx - row * V4;
-            if (row < ROWS) *reinterpret_cast<float4*>(T + row * (WIDTH + 4) + 4 * c4) = v[k];
-        }
-    }
-};
-
 // ---- S = Q Neg^T ---------------------------------------------------------------------------------
-// grid: (negative tiles, row tiles).  Four waves; wave w owns negatives 16w..16w+15 of the tile
+// grid: (tiles of 128 negatives, row tiles).  Four waves; wave w owns negatives 32w..32w+31 of the tile
 // and all row blocks.  S is stored as [row tile][64-negative tile][row][64], so that the tiles the
 // later kernels load are contiguous.
-template <int RB>                             // row blocks of 16 that the tile geometry needs
-__global__ void __launch_bounds__(256, 2)
+// VEC is a template parameter because the compiler made one loop of 32-bit loads of the two branches (four times the load
+// instructions: 217 us a batch of the shape below, more than the matrix work took before).
+template <int RB, bool VEC>                   // row blocks of 16 that the tile geometry needs; d a multiple of four
+__global__ void __launch_bounds__(kGThreads, 3)
 k_gemm_scores(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, const float* __restrict__ Q,
               float* __restrict__ S, int Npad, int nx, int64_t ny) {
-    __shared__ __align__(16) float Qs[kGRows * kGSS];
-    __shared__ __align__(16) float Ns[kGNeg * kGSS];
-    __shared__ int32_t ids_s[kGNeg];
+    using QTile = SplitTile<16 * RB>;
+    using NTile = SplitTile<kGTile>;
+    __shared__ __align__(16) char Qs[QTile::BYTES];
+    __shared__ __align__(16) char Ns[NTile::BYTES];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l15 = lane & 15, gq = lane >> 4;
     int bx;
     int64_t by;
     if (!xcd_tile((int64_t)nx * ny, nx, &bx, &by)) return;       // uniform
     const TileCoord tc = tile_coord(g, by);
-    const int n0 = bx * kGNeg;
+    if (tc.nrows == 0) return;                // uniform: no scores, and nobody reads any
+    const int n0 = bx * kGTile;
     const int N = g.N, d = bp.dim;
     const float* En = tc.side == 0 ? bp.E_dst : bp.E_src;
     const float* Qrows = Q + ((int64_t)tc.si * g.P + tc.e0) * d;
     const int32_t* my_negs = neg_ids + ((int64_t)tc.si * g.nchunks + tc.c) * N;
-    if (tid < kGNeg) ids_s[tid] = my_negs[min(n0 + tid, N - 1)];
-    __syncthreads();
 
-    f32x4 acc[RB];
+    // a thread's share of a slice: elements 8kg..8kg+7 of rows srow, srow + 64 of both operands; rows and negatives that do
+    // not exist are replaced by the last one, and their scores are not written
+    const int srow = tid >> 2, kg = tid & 3;
+    constexpr int QI = (RB + 3) / 4;
+    const float* qrow[QI];
+    const float* nrow[2];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int nrows = tc.nrows;
-    auto q_row = [=](int row) -> const float* { return row < nrows ? Qrows + (int64_t)row * d : nullptr; };
-    const int32_t* ids = ids_s;
-    auto n_row = [=](int row) -> const float* { return n0 + row < N ? En + (int64_t)ids[row] * d : nullptr; };
-    SliceRegs<256, kGRows> qr;
-    SliceRegs<256, kGNeg> nr;
-    qr.fetch(q_row, 0, d, tid);
-    nr.fetch(n_row, 0, d, tid);
-    for (int c0 = 0; c0 < d; c0 += kGSlice) {
-        // slice of Q and of the negatives into LDS (zero beyond the rows / negatives / columns that
-        // exist), the next slice in flight
-        qr.store(Qs, tid);
-        nr.store(Ns, tid);
+    for (int u = 0; u < QI; ++u) qrow[u] = Qrows + (int64_t)min(srow + 64 * u, tc.nrows - 1) * d;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) nrow[u] = En + (int64_t)my_negs[min(n0 + srow + 64 * u, N - 1)] * d;
+    float qv[QI][8], nv[2][8];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int u = 0; u < QI; ++u) load8<VEC>(qrow[u], c0 + 8 * kg, d, qv[u]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) load8<VEC>(nrow[u], c0 + 8 * kg, d, nv[u]);
+    };
+    f32v4 acc[RB][2];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) acc[r][0] = acc[r][1] = f32v4{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    for (int c0 = 0; c0 < d; c0 += kGK) {
+        if (c0 + kGK > d) {                   // components past the end
+#pragma unroll
+            for (int u = 0; u < QI; ++u) zero_past(qv[u], c0 + 8 * kg, d);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) zero_past(nv[u], c0 + 8 * kg, d);
+        }
+#pragma unroll
+        for (int u = 0; u < QI; ++u)
+            if (srow + 64 * u < 16 * RB) QTile::store(Qs, srow + 64 * u, kg, split8(qv[u]));
+#pragma unroll
+        for (int u = 0; u < 2; ++u) NTile::store(Ns, srow + 64 * u, kg, split8(nv[u]));
         __syncthreads();
-        if (c0 + kGSlice < d) {
-            qr.fetch(q_row, c0 + kGSlice, d, tid);
-            nr.fetch(n_row, c0 + kGSlice, d, tid);
-        }
-        const int groups = min(kGSlice, d - c0 + 15) >> 4;
-        const float* nb = Ns + (16 * w + l15) * kGSS + 4 * gq;
-        const float* qa = Qs + l15 * kGSS + 4 * gq;
-        for (int G = 0; G < groups; ++G) {    // all operand reads of a group first, then its MFMAs
-            const float4 b = lds4(nb + 16 * G);
-            float4 a[RB];
-#pragma unroll
-            for (int r = 0; r < RB; ++r) a[r] = lds4(qa + 16 * r * kGSS + 16 * G);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) acc[r] = mfma16g(a[r].x, b.x, acc[r]);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) acc[r] = mfma16g(a[r].y, b.y, acc[r]);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) acc[r] = mfma16g(a[r].z, b.z, acc[r]);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) acc[r] = mfma16g(a[r].w, b.w, acc[r]);
-        }
+        if (c0 + kGK < d) fetch(c0 + kGK);
+        slice_mfma<RB, QTile, NTile>(Qs, Ns, 32 * w, l15, gq, acc);
         __syncthreads();
     }
-    const int n = n0 + 16 * w + l15;
     float* Srow = S + (int64_t)tc.wgrow * g.rows_tile * Npad;
-    if (n < N) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int n = n0 + 32 * w + 16 * b + l15;
+        if (n >= N) continue;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int row = 16 * r + 4 * gq + v;
-                if (row < tc.nrows) Srow[((int64_t)bx * g.rows_tile + row) * kGNeg + 16 * w + l15] = acc[r][v];
+                if (row >= tc.nrows) continue;
+                float s = acc[r][b][v];
+                if (__builtin_expect(s != s, 0)) {
+                    // an infinity took part, or the score is a NaN: the plain sum says which
+                    const float* q = Qrows + (int64_t)row * d;
+                    const float* x = En + (int64_t)my_negs[n] * d;
+                    s = 0.f;
+                    for (int k = 0; k < d; ++k) s = fmaf(q[k], x[k], s);
+                }
+                Srow[((int64_t)(n >> 6) * g.rows_tile + row) * kGNeg + (n & 63)] = s;
             }
         }
     }
@@ -387,156 +373,168 @@ k_gemm_rowstats(BatchGeom g, BucketParams bp, float* __restrict__ S, const float
 }
 
 // ---- G_Q = W Neg ---------------------------------------------------------------------------------
-// grid: (column tiles of CT, row tiles).  CT / 16 waves; wave w owns columns 16w..16w+15 of the
-// tile and all row blocks; the negatives are streamed 64 at a time, the next tile in flight.
-// (A multiple of four waves keeps the four SIMDs of a compute unit evenly loaded between the
-// workgroup barriers.)
-constexpr int kGColTile = 128;            // G_Q: eight waves, 64 KB of LDS, two workgroups per compute unit
-constexpr int kGNegColTile = 80;          // G_neg: five waves; a 128-column Q slice would leave room for one workgroup only (slower)
-template <int CT, int RB>
-__global__ void __launch_bounds__(CT * 4)
+// grid: (tiles of 128 columns, row tiles).  Wave w owns columns 32w..32w+31 of the tile and all row blocks; the negatives
+// are the contraction index, 32 to a slice.
+template <int RB>
+__global__ void __launch_bounds__(kGThreads, 3)
 k_gemm_gq(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, const float* __restrict__ W, int Npad,
           float* __restrict__ GQ, int nx, int64_t ny) {
-    constexpr int THREADS = CT * 4, CS = CT + 4;
-    extern __shared__ __align__(16) float gq_smem[];
-    float* Wt = gq_smem;                      // [112][68]
-    float* Nt = Wt + kGRows * kGWS;           // [64][CT + 4]
+    using WTile = SplitTile<16 * RB>;
+    using NTile = SplitTile<kGTile>;
+    __shared__ __align__(16) char Ws[WTile::BYTES];
+    __shared__ __align__(16) char Ns[NTile::BYTES];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l15 = lane & 15, gq = lane >> 4;
     int bx;
     int64_t by;
     if (!xcd_tile((int64_t)nx * ny, nx, &bx, &by)) return;       // uniform
     const TileCoord tc = tile_coord(g, by);
-    const int c0 = bx * CT;
+    if (tc.nrows == 0) return;                // uniform: no gradient to write
+    const int c0 = bx * kGTile;
     const int N = g.N, d = bp.dim;
     const float* En = tc.side == 0 ? bp.E_dst : bp.E_src;
     const int32_t* my_negs = neg_ids + ((int64_t)tc.si * g.nchunks + tc.c) * N;
     const float* Wtile = W + (int64_t)tc.wgrow * g.rows_tile * Npad;
 
-    WTileRegs<THREADS> wr;
-    SliceRegs<THREADS, kGNeg, CT> nr;
-    auto neg_row = [&](int n0) {
-        return [=](int row) -> const float* { return n0 + row < N ? En + (int64_t)my_negs[n0 + row] * d : nullptr; };
+    // W: eight consecutive negatives of rows srow, srow + 64 (weights past the last negative are zero in the buffer);
+    // negatives: eight rows of one column, rows past the last replaced by it
+    const int srow = tid >> 2, kg = tid & 3;
+    constexpr int WI = (RB + 3) / 4;
+    const float* wrow[WI];
+#pragma unroll
+    for (int u = 0; u < WI; ++u) wrow[u] = Wtile + (int64_t)min(srow + 64 * u, tc.nrows - 1) * kGNeg;
+    const int64_t tile_stride = (int64_t)g.rows_tile * kGNeg;
+    const int col = c0 + (tid & 127);
+    const float* ecol = En + min(col, d - 1);
+    const int kgc = __builtin_amdgcn_readfirstlane(tid >> 7);    // column groups kgc and kgc + 2: one per wave
+    float wv[WI][8], nv[2][8];
+    auto fetch = [&](int n0) {
+        const int64_t off = (int64_t)(n0 >> 6) * tile_stride + (n0 & 63) + 8 * kg;
+#pragma unroll
+        for (int u = 0; u < WI; ++u) load8<true>(wrow[u] + off, 0, 8, wv[u]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                nv[u][t] = ecol[(int64_t)my_negs[min(n0 + 8 * (kgc + 2 * u) + t, N - 1)] * d];
     };
-    wr.fetch(Wtile, g.rows_tile, tc.nrows, 0, tid);
-    nr.fetch(neg_row(0), c0, d, tid);
-
-    f32x4 acc[RB];
+    f32v4 acc[RB][2];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int n0 = 0; n0 < N; n0 += kGNeg) {
-        wr.store(Wt, tid);
-        nr.store(Nt, tid);
+    for (int r = 0; r < RB; ++r) acc[r][0] = acc[r][1] = f32v4{0.f, 0.f, 0.f, 0.f};
+    const bool live = c0 + 32 * w < d;        // uniform per wave
+    fetch(0);
+    for (int n0 = 0; n0 < N; n0 += kGK) {
+#pragma unroll
+        for (int u = 0; u < WI; ++u)
+            if (srow + 64 * u < 16 * RB) WTile::store(Ws, srow + 64 * u, kg, split8(wv[u]));
+#pragma unroll
+        for (int u = 0; u < 2; ++u) NTile::store(Ns, tid & 127, kgc + 2 * u, split8(nv[u]));
         __syncthreads();
-        if (n0 + kGNeg < N) {
-            wr.fetch(Wtile, g.rows_tile, tc.nrows, n0 + kGNeg, tid);
-            nr.fetch(neg_row(n0 + kGNeg), c0, d, tid);
-        }
-        const int groups = c0 + 16 * w < d ? (min(kGNeg, N - n0) + 15) >> 4 : 0;    // nothing for a column block past d
-        const float* wa = Wt + l15 * kGWS + 4 * gq;
-        const float* nb = Nt + (4 * gq) * CS + 16 * w + l15;
-        for (int G = 0; G < groups; ++G) {
-            float b[4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) b[s] = nb[(16 * G + s) * CS];
-            float4 a[RB];
-#pragma unroll
-            for (int r = 0; r < RB; ++r) a[r] = lds4(wa + 16 * r * kGWS + 16 * G);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) acc[r] = mfma16g(a[r].x, b[0], acc[r]);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) acc[r] = mfma16g(a[r].y, b[1], acc[r]);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) acc[r] = mfma16g(a[r].z, b[2], acc[r]);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) acc[r] = mfma16g(a[r].w, b[3], acc[r]);
-        }
+        if (n0 + kGK < N) fetch(n0 + kGK);
+        if (live) slice_mfma<RB, WTile, NTile>(Ws, Ns, 32 * w, l15, gq, acc);
         __syncthreads();
     }
-    const int col = c0 + 16 * w + l15;
-    if (col < d) {
-        float* out = GQ + ((int64_t)tc.si * g.P + tc.e0) * d + col;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int oc = c0 + 32 * w + 16 * b + l15;
+        if (oc >= d) continue;
+        float* out = GQ + ((int64_t)tc.si * g.P + tc.e0) * d + oc;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int row = 16 * r + 4 * gq + v;
-                if (row < tc.nrows) out[(int64_t)row * d] = acc[r][v];
+                if (row < tc.nrows) out[(int64_t)row * d] = acc[r][b][v];
             }
         }
     }
 }
 
 // ---- G_neg = W^T Q -------------------------------------------------------------------------------
-// grid: (column tiles of CT, row tiles).  The Q slice of the column tile stays in LDS; the
-// negatives are walked 64 at a time; wave w owns columns 16w..16w+15 and the four 16-negative
-// blocks of a tile.  Both operands have the contraction index (the row) as the slow one.
-template <int CT>
-__global__ void __launch_bounds__(CT * 4)
+// grid: (tiles of 128 columns x tiles of 128 negatives, row tiles).  The positives are the contraction index: both operands
+// are loaded eight rows of one column (or negative) to a thread.  Wave (wm, wn) owns 64 negatives x 64 columns.
+__global__ void __launch_bounds__(kGThreads, 3)
 k_gemm_gneg(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, const float* __restrict__ W, int Npad,
-            const float* __restrict__ Q, float* __restrict__ grad, int nx, int64_t ny) {
-    extern __shared__ __align__(16) float gneg_smem[];
-    constexpr int THREADS = CT * 4, CS = CT + 4;
-    float* Wt = gneg_smem;                    // [112][68]
-    float* Qs = Wt + kGRows * kGWS;           // [112][CT + 4]
+            const float* __restrict__ Q, float* __restrict__ grad, int ncol, int nx, int64_t ny) {
+    using Tile = SplitTile<kGTile>;
+    __shared__ __align__(16) char Ws[Tile::BYTES];
+    __shared__ __align__(16) char Qs[Tile::BYTES];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l15 = lane & 15, gq = lane >> 4;
+    const int wm = w >> 1, wn = w & 1;
     int bx;
     int64_t by;
     if (!xcd_tile((int64_t)nx * ny, nx, &bx, &by)) return;       // uniform
     const TileCoord tc = tile_coord(g, by);
-    const int c0 = bx * CT;
-    const int N = g.N, d = bp.dim;
+    const int c0 = bx % ncol * kGTile, n0 = bx / ncol * kGTile;
+    const int N = g.N, d = bp.dim, nrows = tc.nrows;
     const int32_t* my_negs = neg_ids + ((int64_t)tc.si * g.nchunks + tc.c) * N;
     const float* Wtile = W + (int64_t)tc.wgrow * g.rows_tile * Npad;
     const float* Qrows = Q + ((int64_t)tc.si * g.P + tc.e0) * d;
-    const int kgroups = (tc.nrows + 15) >> 4;
     const bool atomic = bp.atomic_mode != 0;
     float* Gn = tc.side == 0 ? bp.G_dst : bp.G_src;
     const int64_t neg_base = (int64_t)tc.si * g.per_side + (int64_t)g.roles * g.P + ((int64_t)tc.c * g.T + tc.t_row) * N;
 
-    WTileRegs<THREADS> wr;
-    wr.fetch(Wtile, g.rows_tile, tc.nrows, 0, tid);
-    {
-        SliceRegs<THREADS, kGRows, CT> qr;
-        const int nrows = tc.nrows;
-        qr.fetch([=](int row) -> const float* { return row < nrows ? Qrows + (int64_t)row * d : nullptr; }, c0, d, tid);
-        qr.store(Qs, tid);
-    }
-    const int col = c0 + 16 * w + l15;
-    const bool col0_live = c0 + 16 * w < d;   // uniform per wave
-    for (int n0 = 0; n0 < N; n0 += kGNeg) {
-        __syncthreads();                      // the previous tile's W has been consumed
-        wr.store(Wt, tid);
-        __syncthreads();
-        if (n0 + kGNeg < N) wr.fetch(Wtile, g.rows_tile, tc.nrows, n0 + kGNeg, tid);
-        f32x4 acc[4];
+    const int wcol = min(n0 + (tid & 127), Npad - 1);
+    const float* wp = Wtile + (int64_t)(wcol >> 6) * g.rows_tile * kGNeg + (wcol & 63);
+    const float* qp = Qrows + min(c0 + (tid & 127), d - 1);
+    const int kgc = __builtin_amdgcn_readfirstlane(tid >> 7);
+    float wv[2][8], qv[2][8];
+    auto fetch = [&](int r0) {                // rows past the last one are replaced by it and get weight zero below
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const float* wa = Wt + (4 * gq) * kGWS + l15;
-        const float* qb = Qs + (4 * gq) * CS + 16 * w + l15;
-        for (int G = 0; G < (col0_live ? kgroups : 0); ++G) {    // all operand reads of a group first, then its MFMAs
-            float b[4], a[4][4];
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                b[s] = qb[(16 * G + s) * CS];
-#pragma unroll
-                for (int mb = 0; mb < 4; ++mb) a[s][mb] = wa[(16 * G + s) * kGWS + 16 * mb];
+            for (int t = 0; t < 8; ++t) {
+                const int row = min(r0 + 8 * (kgc + 2 * u) + t, nrows - 1);
+                wv[u][t] = wp[(int64_t)row * kGNeg];
+                qv[u][t] = qp[(int64_t)row * d];
             }
+    };
+    f32v4 acc[4][4];
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int mb = 0; mb < 4; ++mb) acc[mb] = mfma16g(a[s][mb], b[s], acc[mb]);
+        for (int b = 0; b < 4; ++b) acc[a][b] = f32v4{0.f, 0.f, 0.f, 0.f};
+    const int live = min(4, (d - c0 - 64 * wn + 15) >> 4);       // column blocks of this wave, uniform
+    if (nrows > 0) fetch(0);
+    for (int r0 = 0; r0 < nrows; r0 += kGK) {
+        if (r0 + kGK > nrows) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) zero_past(wv[u], r0 + 8 * (kgc + 2 * u), nrows);
         }
-        if (col < d) {
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
+        for (int u = 0; u < 2; ++u) {
+            Tile::store(Ws, tid & 127, kgc + 2 * u, split8(wv[u]));
+            Tile::store(Qs, tid & 127, kgc + 2 * u, split8(qv[u]));
+        }
+        __syncthreads();
+        if (r0 + kGK < nrows) fetch(r0 + kGK);
+        if (live > 0) {
+            Split8 A[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int n = n0 + 16 * mb + 4 * gq + v;
-                    if (n < N) {
-                        if (atomic) unsafeAtomicAdd(Gn + (int64_t)my_negs[n] * d + col, acc[mb][v]);
-                        else grad[(neg_base + n) * d + col] = acc[mb][v];
-                    }
+            for (int a = 0; a < 4; ++a) A[a] = Tile::load(Ws, 64 * wm + 16 * a + l15, gq);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if (b < live) {
+                    Split8 B[1] = {Tile::load(Qs, 64 * wn + 16 * b + l15, gq)};
+                    f32v4 c[4][1] = {{acc[0][b]}, {acc[1][b]}, {acc[2][b]}, {acc[3][b]}};
+                    split_mfma(A, B, c);
+                    acc[0][b] = c[0][0]; acc[1][b] = c[1][0]; acc[2][b] = c[2][0]; acc[3][b] = c[3][0];
                 }
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int col = c0 + 64 * wn + 16 * b + l15;
+        if (col >= d) continue;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int n = n0 + 64 * wm + 16 * a + 4 * gq + v;
+                if (n >= N) continue;
+                if (atomic) unsafeAtomicAdd(Gn + (int64_t)my_negs[n] * d + col, acc[a][b][v]);
+                else grad[(neg_base + n) * d + col] = acc[a][b][v];
             }
         }
     }
@@ -611,19 +609,9 @@ hipError_t launch_chunks_gemm(hipStream_t st, const BatchGeom& g, const BucketPa
     const int64_t tiles = (int64_t)g.sides * g.nchunks * g.T;
     const int64_t rows = (int64_t)g.sides * g.P;
     const int Npad = (int)gemm_npad(g.N);
-    const int ntiles = Npad / kGNeg;
-    const int coltiles = (bp.dim + kGColTile - 1) / kGColTile;
+    const int ntiles = (g.N + kGTile - 1) / kGTile;
+    const int coltiles = (bp.dim + kGTile - 1) / kGTile;
     const bool softmax = bp.loss == LEGEND_LOSS_SOFTMAX;
-    const int negtiles = (bp.dim + kGNegColTile - 1) / kGNegColTile;
-    const size_t gneg_lds = sizeof(float) * (kGRows * kGWS + kGRows * (kGNegColTile + 4));
-    const size_t gq_lds = sizeof(float) * (kGRows * kGWS + kGNeg * (kGColTile + 4));
-    static PerDeviceFlag configured;
-    if (configured.pending()) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_gneg<kGNegColTile>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)gneg_lds);
-        if (e != hipSuccess) return e;
-        configured.set();
-    }
     switch (bp.score) {
         case LEGEND_SCORE_DOT:
             hipLaunchKernelGGL(k_gemm_compose<LEGEND_SCORE_DOT>, dim3((unsigned)rows), dim3(128), 0, st, g, bp, ws.gemm_Q, ws.gemm_f);
@@ -637,14 +625,15 @@ hipError_t launch_chunks_gemm(hipStream_t st, const BatchGeom& g, const BucketPa
     }
     const int rb = (g.rows_tile + 15) / 16;
 #define LEGEND_GEMM_RB(RB)                                                                                             \
-    case RB:                                                                                                           \
-        hipLaunchKernelGGL(k_gemm_scores<RB>, dim3((unsigned)xcd_grid(ntiles * tiles)), dim3(256), 0, st, g, bp, ws.neg_ids, \
+    case RB: {                                                                                                         \
+        auto scores = bp.dim % 4 == 0 ? k_gemm_scores<RB, true> : k_gemm_scores<RB, false>;                            \
+        hipLaunchKernelGGL(scores, dim3((unsigned)xcd_grid(ntiles * tiles)), dim3(kGThreads), 0, st, g, bp, ws.neg_ids, \
                            ws.gemm_Q, ws.gemm_S, Npad, ntiles, tiles);                                                 \
-        break;
-    switch (rb) {
+        break;                                                                                                         \
+    }
+    switch (rb < 7 ? rb : 7) {
         LEGEND_GEMM_RB(1) LEGEND_GEMM_RB(2) LEGEND_GEMM_RB(3) LEGEND_GEMM_RB(4) LEGEND_GEMM_RB(5) LEGEND_GEMM_RB(6)
-        default: hipLaunchKernelGGL(k_gemm_scores<7>, dim3((unsigned)xcd_grid(ntiles * tiles)), dim3(256), 0, st, g, bp,
-                                    ws.neg_ids, ws.gemm_Q, ws.gemm_S, Npad, ntiles, tiles);
+        LEGEND_GEMM_RB(7)
     }
 #undef LEGEND_GEMM_RB
     if (softmax)
@@ -657,28 +646,18 @@ hipError_t launch_chunks_gemm(hipStream_t st, const BatchGeom& g, const BucketPa
         hipLaunchKernelGGL(k_gemm_rowstats<LEGEND_LOSS_LOGISTIC>, dim3((unsigned)tiles), dim3(kStatThreads), 0, st, g, bp,
                            ws.gemm_S, ws.gemm_f, Npad, ws.gemm_a, ws.loss_partial);
 #define LEGEND_GEMM_RB(RB)                                                                                             \
-    case RB: {                                                                                                         \
-        static PerDeviceFlag gq_configured;                                                                            \
-        if (gq_configured.pending()) {                                                                                 \
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_gq<kGColTile, RB>),                         \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)gq_lds);                          \
-            if (e != hipSuccess) return e;                                                                             \
-            gq_configured.set();                                                                                       \
-        }                                                                                                              \
-        hipLaunchKernelGGL((k_gemm_gq<kGColTile, RB>), dim3((unsigned)xcd_grid(coltiles * tiles)), dim3(kGColTile * 4), gq_lds, \
-                           st, g, bp, ws.neg_ids, ws.gemm_S, Npad, ws.gemm_G, coltiles, tiles);                        \
-        break;                                                                                                         \
-    }
-    {
-        hipError_t e = hipSuccess;
-        switch (rb < 7 ? rb : 7) {
-            LEGEND_GEMM_RB(1) LEGEND_GEMM_RB(2) LEGEND_GEMM_RB(3) LEGEND_GEMM_RB(4) LEGEND_GEMM_RB(5) LEGEND_GEMM_RB(6)
-            LEGEND_GEMM_RB(7)
-        }
+    case RB:                                                                                                           \
+        hipLaunchKernelGGL(k_gemm_gq<RB>, dim3((unsigned)xcd_grid(coltiles * tiles)), dim3(kGThreads), 0, st, g, bp,   \
+                           ws.neg_ids, ws.gemm_S, Npad, ws.gemm_G, coltiles, tiles);                                   \
+        break;
+    switch (rb < 7 ? rb : 7) {
+        LEGEND_GEMM_RB(1) LEGEND_GEMM_RB(2) LEGEND_GEMM_RB(3) LEGEND_GEMM_RB(4) LEGEND_GEMM_RB(5) LEGEND_GEMM_RB(6)
+        LEGEND_GEMM_RB(7)
     }
 #undef LEGEND_GEMM_RB
-    hipLaunchKernelGGL(k_gemm_gneg<kGNegColTile>, dim3((unsigned)xcd_grid(negtiles * tiles)), dim3(kGNegColTile * 4), gneg_lds, st, g,
-                       bp, ws.neg_ids, ws.gemm_S, Npad, ws.gemm_Q, ws.grad, negtiles, tiles);
+    const int negtiles = coltiles * ntiles;
+    hipLaunchKernelGGL(k_gemm_gneg, dim3((unsigned)xcd_grid(negtiles * tiles)), dim3(kGThreads), 0, st, g, bp, ws.neg_ids,
+                       ws.gemm_S, Npad, ws.gemm_Q, ws.grad, coltiles, negtiles, tiles);
     switch (bp.score) {
         case LEGEND_SCORE_DOT:
             hipLaunchKernelGGL(k_gemm_chain<LEGEND_SCORE_DOT>, dim3((unsigned)rows), dim3(128), 0, st, g, bp, ws.gemm_Q, ws.gemm_G, ws.gemm_a, ws.grad);
