@@ -471,11 +471,11 @@ k_chunk(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, float
                     const float* src = Ns + rt * QS + gc0;
                     float* dst = grad + (neg_base + neg) * d + gc0;
                     if (vec4) {
-                        *reinterpret_cast<float4*>(dst) = lds4(src);
+                        nt_store4(dst, lds4(src));
                     } else if ((d & 1) == 0) {
                         const float4 v = lds4(src);
-                        *reinterpret_cast<float2*>(dst) = make_float2(v.x, v.y);
-                        if (gc0 + 2 < d) *reinterpret_cast<float2*>(dst + 2) = make_float2(v.z, v.w);
+                        nt_store2(dst, make_float2(v.x, v.y));
+                        if (gc0 + 2 < d) nt_store2(dst + 2, make_float2(v.z, v.w));
                     } else {
                         dst[0] = src[0];
                         if (gc0 + 1 < d) dst[1] = src[1];
