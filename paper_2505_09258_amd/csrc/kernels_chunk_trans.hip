@@ -9,16 +9,15 @@
 //   G_q[e] -= W[e][k] sign(q_e - n_k),   G_neg[k] += W[e][k] sign(q_e - n_k)
 // from one evaluation of every sign.
 //
-// Vector instructions per (positive, negative, component): 2 in either score sweep and 4 in the gradient pass, where
-//     W sign(q - n) = median of (q - n) 2^100, -W and W
-// (one fma, which rounds as the plain difference does, and one med3; a difference of zero gives zero).  That holds while
-// every difference that is not zero is at least W 2^-100: components are zero or between 2^-70 and 2^25 in magnitude,
-// which is checked on the way into LDS, 50 times cheaper than per pair, and W is at most 128.  A tile that fails the
-// check takes the form with a comparison (6 instructions).  Sums are the same, bit for bit, in either form.
-// What is left is lanes that have nothing to do: rows go to lanes in groups of eight (50 rows: 56 of 64), and in the
-// gradient pass a wave takes 16 of the tile's 64 negatives and all components, eight groups of four at a time, the last
-// set shared out over several negatives at once where it has at most four groups (d = 100: 25 groups in 3 1/8 rounds
-// of 8; with the components dealt to the waves instead, one wave in four had one group).
+// In the gradient pass W sign(q - n) is the median of 2^100 (q - n), -W and W: one fma, which rounds as the plain difference does,
+// and one med3, where a comparison for the difference of zero took two instructions more (4 in all against 6 per pair and
+// component).  That holds while every difference that is not zero is at least W 2^-100: components are zero or between 2^-70
+// and 2^25 in magnitude, which is checked on the way into LDS, 50 times cheaper than per pair, and W is at most 128.  A tile
+// that fails the check takes the comparison.  The sums are the same, bit for bit, in either form: a gradient element whose
+// negatives all lie on one side is a difference of equal sums, and Adagrad makes a whole step of its rounding.  (For that
+// reason the negatives of a component also stay with one thread: sharing them out over the waves evens the load, gained
+// little and moved such elements.)  Six batches of 50 000 edges, d = 100, 1000 negatives, with a table read of 48 MB (3 ms of the
+// difference): 20.5 -> 15.7 ms.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -64,11 +63,7 @@ __device__ inline float l1_of(float4 a, float4 b) {
     return (fabsf(a.x - b.x) + fabsf(a.y - b.y)) + (fabsf(a.z - b.z) + fabsf(a.w - b.w));
 }
 
-// Registers bound it at two workgroups per compute unit (d > 64: 255, with spills outside the inner loops).  Fetching the
-// next tile into registers early took more than it gave (600 spills at d = 100).  Six batches of 50 000 edges, d = 100,
-// 1000 negatives, with the table read: 17.3 -> 15.9 ms (before both: comparison form, components dealt to the waves).
-// NS: sets of eight groups of four components; IM: eighths of the rows in use (a row r belongs to slot r / 8)
-template <int LOSS, int NS, int IM>
+template <int LOSS>
 __global__ void __launch_bounds__(kTThreads, 2)
 k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, float* __restrict__ grad,
               double* __restrict__ loss_partial) {
@@ -83,7 +78,6 @@ k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     float* lse_s = pos_s + kTRows;             // [64]
     float* rowloss_s = lse_s + kTRows;         // [64]
     int32_t* odd_s = reinterpret_cast<int32_t*>(rowloss_s + kTRows);    // [4]: some component of q, of the even and of the odd tiles is out of range
-    int32_t* ids_s = odd_s + 4;                // [min(N, kIdsLds)]
 
     const int tid = threadIdx.x;
     int wg = blockIdx.x;
@@ -106,10 +100,7 @@ k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     const int64_t neg_base = side_base + (int64_t)g.roles * g.P + ((int64_t)c * g.T + t) * N;
     const bool vec4 = (d & 3) == 0;
     const float rsign = side == 0 ? 1.f : -1.f;                 // q = x + r or x - r
-    const bool ids_here = N <= kIdsLds;
-    auto neg_id = [&](int n) { return ids_here ? ids_s[n] : my_negs[n]; };
-    if (ids_here)
-        for (int k = tid; k < N; k += kTThreads) ids_s[k] = my_negs[k];
+
     if (tid < 4) odd_s[tid] = 0;
     __syncthreads();
 
@@ -141,15 +132,14 @@ k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
         if (!fine) odd_s[0] = 1;
     }
 
-    // negative tile into Ns; rows past N and columns past d are zero
-    auto gather_tile = [&](int tile) {
-        const int n0 = tile * kTNeg;
+    // negative tile n0..n0+63 into Ns; rows past N and columns past d are zero
+    auto gather_tile = [&](int n0) {
         bool fine = true;
         for (int idx = tid; idx < kTNeg * (QS / 4); idx += kTThreads) {
             const int rt = idx / (QS / 4), c4 = idx % (QS / 4);
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
             if (n0 + rt < N && c4 < d4) {
-                const float* src = Ey + (int64_t)neg_id(n0 + rt) * d + 4 * c4;
+                const float* src = Ey + (int64_t)my_negs[n0 + rt] * d + 4 * c4;
                 if (vec4) {
                     v = *reinterpret_cast<const float4*>(src);
                 } else {
@@ -162,58 +152,63 @@ k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
             *reinterpret_cast<float4*>(Ns + rt * QS + 4 * c4) = v;
             fine = fine && median_range(v.x) && median_range(v.y) && median_range(v.z) && median_range(v.w);
         }
-        if (!fine) odd_s[1 + (tile & 1)] = 1;
-        if (tid == 0) odd_s[1 + ((tile + 1) & 1)] = 0;          // its readers are a barrier behind
+        const int parity = n0 / kTNeg & 1;
+        if (!fine) odd_s[1 + parity] = 1;
+        if (tid == 0) odd_s[2 - parity] = 0;  // the other parity's readers are a barrier behind
     };
-    // scores of rows ty, ty + 8, ... against negatives tx, tx + 32 of the tile
-    const int ty = tid >> 5, tx = tid & 31;
-    auto score_block = [&](float (&S)[IM][2]) {
+    // scores of rows 4ty..4ty+3 against negatives tx, tx+16, tx+32, tx+48 of the tile
+    const int ty = tid >> 4, tx = tid & 15;
+    auto score_block = [&](float (&S)[4][4]) {
 #pragma unroll
-        for (int a = 0; a < IM; ++a) S[a][0] = S[a][1] = 0.f;
-#pragma unroll 1
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) S[a][b] = 0.f;
         for (int j4 = 0; j4 < d4; ++j4) {
-            const float4 n0 = lds4(Ns + tx * QS + 4 * j4), n1 = lds4(Ns + (tx + 32) * QS + 4 * j4);
-            float4 q4[IM];
+            float4 q4[4], n4[4];
 #pragma unroll
-            for (int a = 0; a < IM; ++a) q4[a] = lds4(Qs + (ty + 8 * a) * QS + 4 * j4);
+            for (int a = 0; a < 4; ++a) q4[a] = lds4(Qs + (4 * ty + a) * QS + 4 * j4);
 #pragma unroll
-            for (int a = 0; a < IM; ++a) {
-                S[a][0] += l1_of(q4[a], n0);
-                S[a][1] += l1_of(q4[a], n1);
-            }
+            for (int b = 0; b < 4; ++b) n4[b] = lds4(Ns + (tx + 16 * b) * QS + 4 * j4);
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) S[a][b] += l1_of(q4[a], n4[b]);
         }
 #pragma unroll
-        for (int a = 0; a < IM; ++a) { S[a][0] = -S[a][0]; S[a][1] = -S[a][1]; }
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) S[a][b] = -S[a][b];
     };
     const int ntiles = (N + kTNeg - 1) / kTNeg;
 
     // ---- sweep 1: row-wise log-sum-exp over the negatives (softmax only) ----------------------
     if (LOSS == LEGEND_LOSS_SOFTMAX) {
-        float m[IM], l[IM];
+        float m[4], l[4];
 #pragma unroll
-        for (int a = 0; a < IM; ++a) { m[a] = -INFINITY; l[a] = 0.f; }
+        for (int a = 0; a < 4; ++a) { m[a] = -INFINITY; l[a] = 0.f; }
         for (int tile = 0; tile < ntiles; ++tile) {
             __syncthreads();                  // the previous tile (and, first, Qs) is no longer written / read
-            gather_tile(tile);
+            gather_tile(tile * kTNeg);
             __syncthreads();
-            float S[IM][2];
+            float S[4][4];
             score_block(S);
-            const bool v0 = tile * kTNeg + tx < N, v1 = tile * kTNeg + tx + 32 < N;
-            if (v0) {
 #pragma unroll
-                for (int a = 0; a < IM; ++a) {
-                    const float s1 = v1 ? S[a][1] : -INFINITY;
-                    const float mn = fmaxf(m[a], fmaxf(S[a][0], s1));
-                    l[a] = l[a] * expf(m[a] - mn) + (expf(S[a][0] - mn) + (v1 ? expf(s1 - mn) : 0.f));
-                    m[a] = mn;
+            for (int b = 0; b < 4; ++b) {
+                if (tile * kTNeg + tx + 16 * b < N) {
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        const float mn = fmaxf(m[a], S[a][b]);
+                        l[a] = l[a] * expf(m[a] - mn) + expf(S[a][b] - mn);
+                        m[a] = mn;
+                    }
                 }
             }
         }
-        // the 32 lanes of a row group hold disjoint columns of the same rows
+        // the 16 lanes tx = 0..15 of a row group hold disjoint columns of the same four rows
 #pragma unroll
-        for (int a = 0; a < IM; ++a) {
+        for (int a = 0; a < 4; ++a) {
 #pragma unroll
-            for (int mask = 1; mask < 32; mask <<= 1) {
+            for (int mask = 1; mask < 16; mask <<= 1) {
                 const float mo = wave_shfl_xor(m[a], mask), lo = wave_shfl_xor(l[a], mask);
                 const float mn = fmaxf(m[a], mo);
                 if (mn > -INFINITY) l[a] = l[a] * expf(m[a] - mn) + lo * expf(mo - mn);
@@ -222,196 +217,156 @@ k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
             if (tx == 0) {
                 float mm = m[a], ll = l[a];
                 if (bp.softmax_with_pos) {     // Eq. 1 variant: the positive score is one more term
-                    const float f = pos_s[ty + 8 * a];
+                    const float f = pos_s[4 * ty + a];
                     // lse over the negatives - f: the loss term is its softplus and dL/df minus its sigmoid
-                    rowloss_s[ty + 8 * a] = mm + logf(ll) - f;
+                    rowloss_s[4 * ty + a] = mm + logf(ll) - f;
                     const float mn = fmaxf(mm, f);
                     ll = (mm > -INFINITY ? ll * expf(mm - mn) : 0.f) + expf(f - mn);
                     mm = mn;
                 }
-                lse_s[ty + 8 * a] = mm + logf(ll);
+                lse_s[4 * ty + a] = mm + logf(ll);
             }
         }
     }
 
     // ---- sweep 2: W, G_q and G_neg --------------------------------------------------------------
-    // gradient pass: the 8 lanes of a group (rb = 0..7) share four columns; lane rb owns rows rb, rb + 8, ..., so that
-    // the row slots past the chunk's last row drop out for all lanes at once.  Wave w has negatives 16w..16w+15 of
-    // the tile; in set t, group gi has columns 4 (8t + gi) .. + 3, in the last set gi % share and the share-th part of
-    // the negatives (share = 8, 4, 2 or 1 groups side by side, at least as many as the set has).
-    const int rb = tid & 7, gi = (tid >> 3) & 7, w = tid >> 6;
-    const int last_groups = d4 - 8 * (NS - 1);                  // 1..8
-    const int last_share = last_groups > 4 ? 8 : last_groups > 2 ? 4 : last_groups > 1 ? 2 : 1;
-    float4 accq[NS][IM];
+    // gradient pass: 8 lanes (rb = 0..7) share the four columns 4jg..4jg+3; lane rb owns rows
+    // rb, rb + 8, ..., so that the row groups past the chunk's last row drop out for all lanes at once
+    const int rb = tid & 7, jg = tid >> 3;
+    const bool gactive = jg < d4;
+    const int imax = (nrows + 7) >> 3;
+    float4 accq[8];
 #pragma unroll
-    for (int t = 0; t < NS; ++t)
-#pragma unroll
-        for (int i = 0; i < IM; ++i) accq[t][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < 8; ++i) accq[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     float neg_loss = 0.f;
-    float hinge[IM], viol[IM];                // margin loss: rows ty, ty + 8, ... over this lane's columns
-#pragma unroll
-    for (int a = 0; a < IM; ++a) hinge[a] = viol[a] = 0.f;
+    float hinge[4] = {0.f, 0.f, 0.f, 0.f}, viol[4] = {0.f, 0.f, 0.f, 0.f};    // margin loss: rows 4ty..4ty+3 over this lane's columns
     const bool atomic = bp.atomic_mode != 0;
     const bool weights_fine = LOSS != LEGEND_LOSS_LOGISTIC || fabsf(bp.neg_weight) <= kTMaxWeight;
     float* Gn = side == 0 ? bp.G_dst : bp.G_src;
     for (int tile = 0; tile < ntiles; ++tile) {
         const int n0 = tile * kTNeg;
         __syncthreads();                      // Ns and Wt of the previous tile are no longer read; lse_s is complete
-        gather_tile(tile);
+        gather_tile(n0);
         __syncthreads();
         {
-            float S[IM][2];
+            float S[4][4];
             score_block(S);
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const bool kvalid = n0 + tx + 32 * b < N;
-                float w8[8];
+            for (int b = 0; b < 4; ++b) {
+                const bool kvalid = n0 + tx + 16 * b < N;
+                float w4[4];
 #pragma unroll
-                for (int a = 0; a < 8; ++a) w8[a] = 0.f;
-#pragma unroll
-                for (int a = 0; a < IM; ++a) {
-                    if (kvalid && ty + 8 * a < nrows) {
+                for (int a = 0; a < 4; ++a) {
+                    const bool valid = kvalid && 4 * ty + a < nrows;
+                    float w = 0.f;
+                    if (valid) {
                         if (LOSS == LEGEND_LOSS_SOFTMAX) {
-                            w8[a] = expf(S[a][b] - lse_s[ty + 8 * a]);
+                            w = expf(S[a][b] - lse_s[4 * ty + a]);
                         } else if (LOSS == LEGEND_LOSS_MARGIN) {
                             // the pair pays margin - f + S where that is positive; W is the indicator
-                            const float sh = (bp.margin - pos_s[ty + 8 * a]) + S[a][b];
-                            w8[a] = sh > 0.f ? 1.f : 0.f;
+                            const float sh = (bp.margin - pos_s[4 * ty + a]) + S[a][b];
+                            w = sh > 0.f ? 1.f : 0.f;
                             hinge[a] += fmaxf(sh, 0.f);
-                            viol[a] += w8[a];
+                            viol[a] += w;
                         } else {
-                            w8[a] = bp.neg_weight * sigmoidf(S[a][b]);
+                            w = bp.neg_weight * sigmoidf(S[a][b]);
                             neg_loss += bp.neg_weight * softplusf(S[a][b]);
                         }
                     }
+                    w4[a] = w;
                 }
                 // row r sits at position (r % 8) * 8 + r / 8: the eight rows of a lane of the gradient pass are adjacent
-                float* wt = Wt + (tx + 32 * b) * kTWS + 8 * ty;
-                *reinterpret_cast<float4*>(wt) = make_float4(w8[0], w8[1], w8[2], w8[3]);
-                *reinterpret_cast<float4*>(wt + 4) = make_float4(w8[4], w8[5], w8[6], w8[7]);
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const int r = 4 * ty + a;
+                    Wt[(tx + 16 * b) * kTWS + (r & 7) * 8 + (r >> 3)] = w4[a];
+                }
             }
         }
         __syncthreads();
-        const bool median = weights_fine && !(odd_s[0] | odd_s[1 + (tile & 1)]);    // uniform
         auto pass = [&](auto Median) __attribute__((always_inline)) {
+            float4 q[8];
 #pragma unroll
-            for (int t = 0; t < NS; ++t) {
-                const int share = t == NS - 1 ? last_share : 8;
-                const int jg = 8 * t + (gi & (share - 1));
-                const bool live = jg < d4;
-                const int col = 4 * (live ? jg : 0);
-                const int step = 8 / share;   // negatives taken side by side
-                asm volatile("" ::: "memory");        // the rows of one set in registers at a time
-                float4 q[IM];
+            for (int i = 0; i < 8; ++i) {
+                q[i] = lds4(Qs + (rb + 8 * i) * QS + 4 * jg);
+                if (decltype(Median)::value) { q[i].x *= kTScale; q[i].y *= kTScale; q[i].z *= kTScale; q[i].w *= kTScale; }
+            }
+            auto weighted = [](float qc, float nc, float wk) __attribute__((always_inline)) {
+                if (decltype(Median)::value) return __builtin_amdgcn_fmed3f(fmaf(nc, -kTScale, qc), -wk, wk);
+                return sign_times(qc - nc, wk);
+            };
+            for (int k = 0; k < kTNeg; ++k) {
+                const float4 n4 = lds4(Ns + k * QS + 4 * jg);
+                const float4 wa = lds4(Wt + k * kTWS + 8 * rb), wb = lds4(Wt + k * kTWS + 8 * rb + 4);
+                const float w8[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+                float4 pn = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-                for (int i = 0; i < IM; ++i) {
-                    q[i] = lds4(Qs + (rb + 8 * i) * QS + col);
-                    if (decltype(Median)::value) { q[i].x *= kTScale; q[i].y *= kTScale; q[i].z *= kTScale; q[i].w *= kTScale; }
-                }
-#pragma unroll 1
-                for (int k = 16 * w + gi / share; k < 16 * w + 16; k += step) {
-                    const float4 n4 = lds4(Ns + k * QS + col);
-                    const float4 wa = lds4(Wt + k * kTWS + 8 * rb), wb = lds4(Wt + k * kTWS + 8 * rb + 4);
-                    const float w8[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
-                    float4 pn = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                    for (int i = 0; i < IM; ++i) {
-                        auto one = [&](float qc, float nc, float& aq, float& ap) __attribute__((always_inline)) {
-                            float tv;
-                            if (decltype(Median)::value) tv = __builtin_amdgcn_fmed3f(fmaf(nc, -kTScale, qc), -w8[i], w8[i]);
-                            else tv = sign_times(qc - nc, w8[i]);
-                            aq -= tv;
-                            ap += tv;
-                        };
-                        one(q[i].x, n4.x, accq[t][i].x, pn.x);
-                        one(q[i].y, n4.y, accq[t][i].y, pn.y);
-                        one(q[i].z, n4.z, accq[t][i].z, pn.z);
-                        one(q[i].w, n4.w, accq[t][i].w, pn.w);
+                for (int i = 0; i < 8; ++i) {
+                    if (i < imax) {
+                        float tv;
+                        tv = weighted(q[i].x, n4.x, w8[i]); accq[i].x -= tv; pn.x += tv;
+                        tv = weighted(q[i].y, n4.y, w8[i]); accq[i].y -= tv; pn.y += tv;
+                        tv = weighted(q[i].z, n4.z, w8[i]); accq[i].z -= tv; pn.z += tv;
+                        tv = weighted(q[i].w, n4.w, w8[i]); accq[i].w -= tv; pn.w += tv;
                     }
-                    // the rows of the eight lanes of the group, in a fixed order
-                    pn.x = sum8(pn.x);
-                    pn.y = sum8(pn.y);
-                    pn.z = sum8(pn.z);
-                    pn.w = sum8(pn.w);
-                    if (rb == 0 && live && n0 + k < N) {
-                        if (atomic) {
-                            float* dst = Gn + (int64_t)my_negs[n0 + k] * d + col;
-                            unsafeAtomicAdd(dst, pn.x);
-                            if (col + 1 < d) unsafeAtomicAdd(dst + 1, pn.y);
-                            if (col + 2 < d) unsafeAtomicAdd(dst + 2, pn.z);
-                            if (col + 3 < d) unsafeAtomicAdd(dst + 3, pn.w);
+                }
+                // the rows of the eight lanes of the group, in a fixed order
+                pn.x = sum8(pn.x);
+                pn.y = sum8(pn.y);
+                pn.z = sum8(pn.z);
+                pn.w = sum8(pn.w);
+                if (rb == 0 && n0 + k < N) {
+                    const int col = 4 * jg;
+                    if (atomic) {
+                        float* dst = Gn + (int64_t)my_negs[n0 + k] * d + col;
+                        unsafeAtomicAdd(dst, pn.x);
+                        if (col + 1 < d) unsafeAtomicAdd(dst + 1, pn.y);
+                        if (col + 2 < d) unsafeAtomicAdd(dst + 2, pn.z);
+                        if (col + 3 < d) unsafeAtomicAdd(dst + 3, pn.w);
+                    } else {
+                        float* dst = grad + (neg_base + n0 + k) * d + col;
+                        if (vec4) {
+                            nt_store4(dst, pn);
                         } else {
-                            float* dst = grad + (neg_base + n0 + k) * d + col;
-                            if (vec4) {
-                                *reinterpret_cast<float4*>(dst) = pn;
-                            } else {
-                                dst[0] = pn.x;
-                                if (col + 1 < d) dst[1] = pn.y;
-                                if (col + 2 < d) dst[2] = pn.z;
-                                if (col + 3 < d) dst[3] = pn.w;
-                            }
+                            dst[0] = pn.x;
+                            if (col + 1 < d) dst[1] = pn.y;
+                            if (col + 2 < d) dst[2] = pn.z;
+                            if (col + 3 < d) dst[3] = pn.w;
                         }
                     }
                 }
             }
         };
-        if (__builtin_expect(median, 1)) pass(std::true_type{});
-        else pass(std::false_type{});
+        if (gactive) {
+            // uniform over the workgroup
+            if (__builtin_expect(weights_fine && !(odd_s[0] | odd_s[1 + (tile & 1)]), 1)) pass(std::true_type{});
+            else pass(std::false_type{});
+        }
     }
 
     // ---- epilogue: G_q to LDS, positive terms, chain rule, gradient rows of the positives -------
     __syncthreads();                          // the last tile is no longer read
-    // the negatives of a row's sum lie with four waves, and in the last set with the groups that share its columns
     float* Gs = Ns;
-    {
-        const int t = NS - 1;
-        for (int mask = 8 * last_share; mask < kWave; mask <<= 1) {
+    if (gactive) {
 #pragma unroll
-            for (int i = 0; i < IM; ++i) {
-                accq[t][i].x += wave_shfl_xor(accq[t][i].x, mask);
-                accq[t][i].y += wave_shfl_xor(accq[t][i].y, mask);
-                accq[t][i].z += wave_shfl_xor(accq[t][i].z, mask);
-                accq[t][i].w += wave_shfl_xor(accq[t][i].w, mask);
-            }
-        }
-    }
-    for (int ww = 0; ww < kTThreads / kWave; ++ww) {
-        if (w == ww) {
-#pragma unroll
-            for (int t = 0; t < NS; ++t) {
-                const int jg = 8 * t + gi;
-                if (jg < d4) {
-#pragma unroll
-                    for (int i = 0; i < IM; ++i) {
-                        float4* p = reinterpret_cast<float4*>(Gs + (rb + 8 * i) * QS + 4 * jg);
-                        float4 v = accq[t][i];
-                        if (ww > 0) {
-                            const float4 o = *p;
-                            v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-                        }
-                        *p = v;
-                    }
-                }
-            }
-        }
-        __syncthreads();
+        for (int i = 0; i < 8; ++i) *reinterpret_cast<float4*>(Gs + (rb + 8 * i) * QS + 4 * jg) = accq[i];
     }
     if (LOSS == LEGEND_LOSS_LOGISTIC) {
         for (int off = kWave / 2; off > 0; off >>= 1) neg_loss += __shfl_down(neg_loss, off, kWave);
         if ((tid & 63) == 0) lse_s[tid >> 6] = neg_loss;
     }
     if (LOSS == LEGEND_LOSS_MARGIN) {
-        // the 32 lanes of a row group hold disjoint columns of the same rows
+        // the 16 lanes tx = 0..15 of a row group hold disjoint columns of the same four rows
 #pragma unroll
-        for (int a = 0; a < IM; ++a) {
+        for (int a = 0; a < 4; ++a) {
 #pragma unroll
-            for (int mask = 1; mask < 32; mask <<= 1) {
+            for (int mask = 1; mask < 16; mask <<= 1) {
                 hinge[a] += wave_shfl_xor(hinge[a], mask);
                 viol[a] += wave_shfl_xor(viol[a], mask);
             }
             if (tx == 0) {
-                lse_s[ty + 8 * a] = hinge[a];         // the row's loss term
-                rowloss_s[ty + 8 * a] = viol[a];      // how many of its negatives pay: -dL/df
+                lse_s[4 * ty + a] = hinge[a];         // the row's loss term
+                rowloss_s[4 * ty + a] = viol[a];      // how many of its negatives pay: -dL/df
             }
         }
     }
@@ -471,48 +426,31 @@ k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     }
 }
 
-template <int LOSS, int NS, int IM>
+template <int LOSS>
 hipError_t launch_trans(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {
     const int QS = chunk_row_stride(bp.dim);
-    const size_t lds = sizeof(float) * ((size_t)(kTRows + kTNeg) * QS + (size_t)kTNeg * kTWS + 3 * kTRows + 4 +
-                                        (g.N <= kIdsLds ? g.N : 0));
+    const size_t lds = sizeof(float) * ((size_t)(kTRows + kTNeg) * QS + (size_t)kTNeg * kTWS + 3 * kTRows + 4);
     static size_t lds_allowed[64] = {};       // dynamic LDS above 64 KB has to be requested per kernel and per device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
     if (dev < 0 || lds > lds_allowed[dev]) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chunk_trans<LOSS, NS, IM>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chunk_trans<LOSS>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         if (dev >= 0) lds_allowed[dev] = lds;
     }
-    hipLaunchKernelGGL((k_chunk_trans<LOSS, NS, IM>), dim3((unsigned)(g.sides * g.nchunks * g.T)), dim3(kTThreads), lds, st, g, bp,
+    hipLaunchKernelGGL(k_chunk_trans<LOSS>, dim3((unsigned)(g.sides * g.nchunks * g.T)), dim3(kTThreads), lds, st, g, bp,
                        ws.neg_ids, ws.grad, ws.loss_partial);
     return hipGetLastError();
-}
-
-// row slots by the tile's rows: the whole tile, at most 56 rows (the chunks of 50) or at most 32
-template <int LOSS, int NS>
-hipError_t launch_trans_rows(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {
-    if (g.rows_tile <= 32) return launch_trans<LOSS, NS, 4>(st, g, bp, ws);
-    if (g.rows_tile <= 56) return launch_trans<LOSS, NS, 7>(st, g, bp, ws);
-    return launch_trans<LOSS, NS, 8>(st, g, bp, ws);
-}
-
-template <int LOSS>
-hipError_t launch_trans_dim(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {
-    if (bp.dim <= 32) return launch_trans_rows<LOSS, 1>(st, g, bp, ws);
-    if (bp.dim <= 64) return launch_trans_rows<LOSS, 2>(st, g, bp, ws);
-    if (bp.dim <= 96) return launch_trans_rows<LOSS, 3>(st, g, bp, ws);
-    return launch_trans_rows<LOSS, 4>(st, g, bp, ws);
 }
 
 }  // namespace
 
 hipError_t launch_chunks_trans(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {
     if (bp.dim > kNarrowMaxDim || g.rows_tile > kTRows) return hipErrorInvalidValue;
-    if (bp.loss == LEGEND_LOSS_LOGISTIC) return launch_trans_dim<LEGEND_LOSS_LOGISTIC>(st, g, bp, ws);
-    if (bp.loss == LEGEND_LOSS_MARGIN) return launch_trans_dim<LEGEND_LOSS_MARGIN>(st, g, bp, ws);
-    return launch_trans_dim<LEGEND_LOSS_SOFTMAX>(st, g, bp, ws);
+    if (bp.loss == LEGEND_LOSS_LOGISTIC) return launch_trans<LEGEND_LOSS_LOGISTIC>(st, g, bp, ws);
+    if (bp.loss == LEGEND_LOSS_MARGIN) return launch_trans<LEGEND_LOSS_MARGIN>(st, g, bp, ws);
+    return launch_trans<LEGEND_LOSS_SOFTMAX>(st, g, bp, ws);
 }
 
 }  // namespace legend
