@@ -28,11 +28,12 @@ struct HostCopyPart {
 
 class HostCopyRing {
 public:
-    static constexpr size_t kBlock = (size_t)2 << 20;
-    static constexpr int kSlots = 12;
+    static constexpr size_t kBlock = (size_t)1 << 20;
+    static constexpr int kSlots = 8;
     static constexpr int kMaxThreads = 8;
-    // Below this a plain hipMemcpy is as good: starting the threads takes about 0.1 ms, the time of 1.5 MB.
-    static constexpr size_t kMinBytes = (size_t)4 << 20;
+    // A context's first large read also pays for pinning the ring, about 0.1 ms a MB (with 24 MB of ring a first read of 24 MB was
+    // slower than hipMemcpy); 32 MB take hipMemcpy 2 to 3 ms.
+    static constexpr size_t kMinBytes = (size_t)32 << 20;
 
     // pinned memory and events on first use; false (nothing kept) where the host cannot give them
     bool prepare() {

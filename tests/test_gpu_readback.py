@@ -6,8 +6,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# 4 MB is the smallest read that takes the ring, 24 MB one full ring of 2 MB blocks
-@pytest.mark.parametrize("V,d,n,capacity", [(8_191, 128, 1, 1), (8_192, 128, 1, 1), (98_304, 64, 1, 1), (98_305, 64, 3, 3),
+# 32 MB is the smallest read that takes the ring of 1 MB blocks
+@pytest.mark.parametrize("V,d,n,capacity", [(65_535, 128, 1, 1), (65_536, 128, 1, 1), (65_537, 128, 1, 1), (180_001, 64, 3, 3),
                                             (400_003, 50, 5, 3)])
 def test_whole_table_read_returns_the_table(V, d, n, capacity):
     from paper_2505_09258_amd import binding as L
