@@ -72,15 +72,24 @@ CASES = [
 ]
 
 _TRANS_EDGES = [
-    # translational score at the edges of its column sets (32 columns each) and row slots (32, 56 and 64 rows), and with
-    # components below 2^-70, for which the signs are compared instead (margin: no multiple of the 0.1 that a first Adagrad
-    # step moves every component by, so that no pair of the second batch sits on the hinge)
+    # translational score at odd dimensions and row counts on both sides of its groups of eight rows, and with components below
+    # 2^-70, for which the signs are compared instead (margin: no multiple of the 0.1 that a first Adagrad step moves every
+    # component by, so that no pair of the second batch sits on the hinge)
     _case("transe_d1_rows32", TRANSE, SOFTMAX, DST, 900, 3, 1, 1, 0, 0, 96, 32, 63, 0, 200, 0.3),
     _case("transe_d33_rows33", TRANSE, SOFTMAX, BOTH, 1_500, 3, 33, 1, 0, 0, 132, 33, 64, 0, 300, 0.3),
     _case("transe_d64_rows56", TRANSE, SOFTMAX, SRC, 1_500, 3, 64, 1, 0, 0, 168, 56, 65, 5, 400, 0.3),
     _case("transe_d68_rows57", TRANSE, LOGISTIC, DST, 1_500, 3, 68, 1, 0, 0, 171, 57, 130, 5, 400, 0.3),
     _case("transe_d97_rows64", TRANSE, SOFTMAX, DST, 1_500, 3, 97, 1, 0, 0, 192, 64, 100, 0, 400, 0.3),
     dict(_case("transe_d36_tiny_components", TRANSE, MARGIN, BOTH, 1_500, 3, 36, 1, 0, 0, 150, 50, 70, 0, 300, 1e-23), margin=1.03),
+]
+
+# The wide path at the edges of its tiles: 128 negatives, 128 columns, slices of 32, row blocks of 16 up to 112.
+_WIDE_EDGES = [
+    _case("dot_d129_n127_rows16", DOT, SOFTMAX, DST, 900, 0, 129, 1, 0, 0, 64, 16, 127, 0, 150, 0.2),
+    _case("distmult_d160_n128_rows17", DISTMULT, SOFTMAX, BOTH, 900, 3, 160, 1, 0, 0, 68, 17, 128, 5, 150, 0.2),
+    _case("complex_d130_n129_rows112", COMPLEX, LOGISTIC, BOTH, 900, 3, 130, 1, 0, 0, 224, 112, 129, 0, 300, 0.2),
+    _case("dot_d256_n1_rows113", DOT, SOFTMAX_POS, SRC, 900, 0, 256, 1, 0, 0, 226, 113, 1, 0, 300, 0.2),
+    _case("distmult_d388_n257_rows33", DISTMULT, SOFTMAX, DST, 900, 3, 388, 1, 0, 0, 66, 33, 257, 0, 140, 0.15),
 ]
 
 # One node row in 64 is four times larger than the rest, so that some chunks hold a score far
@@ -169,6 +178,11 @@ def test_every_batch_matches_oracle(c):
 
 @pytest.mark.parametrize("c", _TRANS_EDGES, ids=[c["name"] for c in _TRANS_EDGES])
 def test_translational_kernel_at_its_edges(c):
+    _check_every_batch(c)
+
+
+@pytest.mark.parametrize("c", _WIDE_EDGES, ids=[c["name"] for c in _WIDE_EDGES])
+def test_wide_path_at_its_tile_edges(c):
     _check_every_batch(c)
 
 
