@@ -320,20 +320,21 @@ k_long_final(const uint32_t* __restrict__ counters, const uint32_t* __restrict__
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
             const uint32_t last = unit_start[r + 1];
             const int cols = min(4, d - cc);
-            for (uint32_t unit = unit_start[r]; unit < last; unit += 8) {
+            uint32_t unit = unit_start[r];
+            for (; unit + 8 <= last; unit += 8) {
                 double v[8][4];
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        v[k][j] = partial[(int64_t)min(unit + k, last - 1) * d + cc + min(j, cols - 1)];
+                    for (int j = 0; j < 4; ++j) v[k][j] = partial[(int64_t)(unit + k) * d + cc + min(j, cols - 1)];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    if (unit + k < last) {
+                for (int k = 0; k < 8; ++k)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) acc[j] += v[k][j];
-                    }
-                }
+                    for (int j = 0; j < 4; ++j) acc[j] += v[k][j];
+            }
+            for (; unit < last; ++unit) {     // most long rows have one unit
+                const double* pp = partial + (int64_t)unit * d + cc;
+                for (int j = 0; j < cols; ++j) acc[j] += pp[j];
             }
             apply_row(tb, uniq_keys[long_list[r]], acc, d, cc, vec4, lr, eps);
         }
