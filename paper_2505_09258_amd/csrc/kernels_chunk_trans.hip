@@ -12,8 +12,10 @@
 // In the gradient pass W sign(q - n) is the median of 2^100 (q - n), -W and W: one fma, which rounds as the plain difference does,
 // and one med3, where a comparison for the difference of zero took two instructions more (4 in all against 6 per pair and
 // component).  That holds while every difference that is not zero is at least W 2^-100: components are zero or between 2^-70
-// and 2^25 in magnitude, which is checked on the way into LDS, 50 times cheaper than per pair, and W is at most 128.  A tile
-// that fails the check takes the comparison.  The sums are the same, bit for bit, in either form: a gradient element whose
+// and 2^25 in magnitude, which is checked on the way into LDS, 50 times cheaper than per pair, and W is at most 128 and no NaN
+// (the median of a NaN weight would be the difference; with components in range a weight is NaN only where a NaN in the
+// replaced endpoint's row enters the log-sum-exp as the positive score).  A tile that fails the check takes the
+// comparison.  The sums are the same, bit for bit, in either form: a gradient element whose
 // negatives all lie on one side is a difference of equal sums, and Adagrad makes a whole step of its rounding.  (For that
 // reason the negatives of a component also stay with one thread: sharing them out over the waves evens the load, gained
 // little and moved such elements.)  Six batches of 50 000 edges, d = 100, 1000 negatives, with a table read of 48 MB (3 ms of the
@@ -77,7 +79,7 @@ k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     float* pos_s = Wt + kTNeg * kTWS;          // [64]
     float* lse_s = pos_s + kTRows;             // [64]
     float* rowloss_s = lse_s + kTRows;         // [64]
-    int32_t* odd_s = reinterpret_cast<int32_t*>(rowloss_s + kTRows);    // [4]: some component of q, of the even and of the odd tiles is out of range
+    int32_t* odd_s = reinterpret_cast<int32_t*>(rowloss_s + kTRows);    // [4]: some component of q (or row's log-sum-exp), of the even and of the odd tiles is out of range
 
     const int tid = threadIdx.x;
     int wg = blockIdx.x;
@@ -224,7 +226,9 @@ k_chunk_trans(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
                     ll = (mm > -INFINITY ? ll * expf(mm - mn) : 0.f) + expf(f - mn);
                     mm = mn;
                 }
-                lse_s[4 * ty + a] = mm + logf(ll);
+                const float lse = mm + logf(ll);
+                lse_s[4 * ty + a] = lse;
+                if (lse != lse) odd_s[0] = 1;  // a NaN positive score: the weights of its row are NaN
             }
         }
     }
