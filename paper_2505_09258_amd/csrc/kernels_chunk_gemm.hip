@@ -54,6 +54,11 @@ __device__ inline void zero_past(float (&v)[8], int k, int n) {
         if (k + t >= n) v[t] = 0.f;
 }
 
+__device__ inline bool any_nan(f32v4 x) {
+    const float s = (x[0] + x[1]) + (x[2] + x[3]);          // inf - inf as well: a look too many, no harm
+    return s != s;
+}
+
 // acc[a][b] += A_a B_b^T of one slice for RA blocks of 16 rows (of which two at a time are in registers) and two blocks
 // of 16 columns
 template <int RA, class TA, class TB>
@@ -224,6 +229,14 @@ k_gemm_scores(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
         slice_mfma<RB, QTile, NTile>(Qs, Ns, 32 * w, l15, gq, acc);
         __syncthreads();
     }
+    bool nan = false;                         // an infinity took part, or the score is a NaN
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) nan |= any_nan(acc[r][b]);
+    if (__builtin_expect(__any(nan), 0))
+        plain_products(d, [&](int r, int k) { return Qrows[(int64_t)min(16 * r + l15, tc.nrows - 1) * d + k]; },
+                       [&](int b, int k) { return En[(int64_t)my_negs[min(n0 + 32 * w + 16 * b + l15, N - 1)] * d + k]; }, acc);
     float* Srow = S + (int64_t)tc.wgrow * g.rows_tile * Npad;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
@@ -234,16 +247,7 @@ k_gemm_scores(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int row = 16 * r + 4 * gq + v;
-                if (row >= tc.nrows) continue;
-                float s = acc[r][b][v];
-                if (__builtin_expect(s != s, 0)) {
-                    // an infinity took part, or the score is a NaN: the plain sum says which
-                    const float* q = Qrows + (int64_t)row * d;
-                    const float* x = En + (int64_t)my_negs[n] * d;
-                    s = 0.f;
-                    for (int k = 0; k < d; ++k) s = fmaf(q[k], x[k], s);
-                }
-                Srow[((int64_t)(n >> 6) * g.rows_tile + row) * kGNeg + (n & 63)] = s;
+                if (row < tc.nrows) Srow[((int64_t)(n >> 6) * g.rows_tile + row) * kGNeg + (n & 63)] = acc[r][b][v];
             }
         }
     }
@@ -433,6 +437,14 @@ k_gemm_gq(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, con
         if (live) slice_mfma<RB, WTile, NTile>(Ws, Ns, 32 * w, l15, gq, acc);
         __syncthreads();
     }
+    bool nan = false;
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) nan |= any_nan(acc[r][b]);
+    if (__builtin_expect(__any(nan), 0))
+        plain_products(N, [&](int r, int k) { return Wtile[(k >> 6) * tile_stride + min(16 * r + l15, tc.nrows - 1) * kGNeg + (k & 63)]; },
+                       [&](int b, int k) { return En[(int64_t)my_negs[k] * d + min(c0 + 32 * w + 16 * b + l15, d - 1)]; }, acc);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         const int oc = c0 + 32 * w + 16 * b + l15;
@@ -523,6 +535,18 @@ k_gemm_gneg(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, c
         }
         __syncthreads();
     }
+    bool nan = false;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) nan |= any_nan(acc[a][b]);
+    if (__builtin_expect(__any(nan), 0))
+        plain_products(nrows,
+            [&](int a, int k) {
+                const int n = min(n0 + 64 * wm + 16 * a + l15, Npad - 1);
+                return Wtile[((n >> 6) * g.rows_tile + k) * kGNeg + (n & 63)];
+            },
+            [&](int b, int k) { return Qrows[(int64_t)k * d + min(c0 + 64 * wn + 16 * b + l15, d - 1)]; }, acc);
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         const int col = c0 + 64 * wn + 16 * b + l15;
