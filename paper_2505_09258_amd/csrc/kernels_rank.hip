@@ -277,7 +277,9 @@ k_rank(const float* __restrict__ Q, const float* __restrict__ f, const int32_t* 
 #pragma unroll
                 for (int v = 0; v < 4; ++v) sum += acc[a][b][v];
             if (__builtin_expect(sum != sum, 0)) {
-                // an infinity took part, or a score is a NaN: the plain sums of the candidates that count say which
+                // An infinity took part, or a score is a NaN: the plain sums of the candidates that count say which.  A sum ends
+                // at its first NaN: a diverged table's rows are NaN from the first component on (3000 triples, 6000
+                // candidates, d = 256: 0.11 ms finite, 0.15 ms all NaN, 11 ms when every sum was carried to its end).
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     if (cid[v] < 0) continue;
@@ -289,7 +291,7 @@ k_rank(const float* __restrict__ Q, const float* __restrict__ f, const int32_t* 
                         const int64_t r = row0 + 64 * wn + 16 * b + li;
                         const float* q = Q + (r < m_pad ? r : m_pad - 1) * dp;
                         float s = 0.f;
-                        for (int k = 0; k < d; ++k) s = fmaf(q[k], x[k], s);
+                        for (int k = 0; k < d && s == s; ++k) s = fmaf(q[k], x[k], s);
                         acc[a][b][v] = s;
                     }
                 }

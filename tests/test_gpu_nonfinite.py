@@ -125,3 +125,29 @@ def test_wide_path_time_on_a_diverged_table(share):
     node[rng.random(4_000) < share] = np.nan
     nan = _train_ms(node, loss=LOGISTIC)
     assert nan < 4 * finite
+
+
+@pytest.mark.parametrize("share", [1.0, 0.01])
+def test_rank_time_on_a_diverged_table(share):
+    """The same for ranks."""
+    from paper_2505_09258_amd import binding as L
+    rng = np.random.default_rng(3)
+    V, d, m = 6_000, 256, 3_000
+    src, dst = rng.integers(0, V, m), rng.integers(0, V, m)
+    node = (0.1 * rng.standard_normal((V, d))).astype(np.float32)
+    ms = []
+    for nan in (False, True):
+        if nan:
+            node[rng.random(V) < share] = np.nan
+        cfg = L.make_config(num_nodes=V, dim=d, batch_size=1_000, chunk_size=50, num_negs=50, score=DOT, seed=1)
+        ctx = L.legend_init_partitions(cfg, node, None)
+        try:
+            L.legend_swap_partition(ctx, -1, 0)
+            L.legend_rank_edges(ctx, src, None, dst, DST, None)
+            out = [L.legend_rank_edges(ctx, src, None, dst, DST, None) for _ in range(3)]
+        finally:
+            L.legend_destroy(ctx)
+        ms.append(min(x[2]["ms"] for x in out))
+    lost = np.isnan(node[src, 0]) | np.isnan(node[dst, 0])
+    assert not out[0][0][lost].any() and not out[0][1][lost].any()
+    assert ms[1] < 4 * ms[0]
