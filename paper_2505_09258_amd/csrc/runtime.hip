@@ -230,19 +230,8 @@ int ensure_io(legend_ctx* c, size_t bytes) {
     return LEGEND_OK;
 }
 
-// Device and host-tier memory into the caller's memory; every stream that could write the parts is idle.  Large reads
-// take the pinned ring (1M x 100 floats: 25 to 38 ms by hipMemcpy), small ones plain copies.
 int read_parts(legend_ctx* c, const std::vector<HostCopyPart>& parts) {
-    size_t total = 0;
-    for (const HostCopyPart& p : parts) total += p.bytes;
-    if (total >= HostCopyRing::kMinBytes && c->readback.prepare()) {
-        HIP_TRY(c, c->readback.run(parts, c->cfg.device, c->copy_out));
-        return LEGEND_OK;
-    }
-    for (const HostCopyPart& p : parts) {
-        if (p.on_device) HIP_TRY(c, hipMemcpy(p.dst, p.src, p.bytes, hipMemcpyDeviceToHost));
-        else std::memcpy(p.dst, p.src, p.bytes);
-    }
+    HIP_TRY(c, copy_parts(c->readback, parts, c->cfg.device, c->copy_out));
     return LEGEND_OK;
 }
 
