@@ -27,21 +27,51 @@ __device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
 
 __device__ inline float wave_shfl_xor(float v, int mask) { return __shfl_xor(v, mask, kWave); }
 
-// Gradient rows are written once and read once, by the next kernel, and a large batch has more of them (440 MB at 1.1M rows of
-// 100 floats) than the caches hold: their loads and stores are marked as streaming, so that they displace less of the
-// embedding tables (large social shape 100 -> 98 ms an epoch of 100 batches, ComplEx on both sides 77.8 -> 75.4, staged
-// 40.1 -> 37.7 together with the unrolled sum of the long rows' units).
+// Gradient rows are written once and read once, by the next kernel.  Where they and the tables do not fit the caches together
+// (BucketParams::stream_rows), their loads and stores are marked as streaming, so that they displace less of the tables.
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
 typedef float nt_f2 __attribute__((ext_vector_type(2)));
-__device__ inline float4 nt_load4(const float* p) {
+template <bool STREAM>
+__device__ inline float4 row_load4(const float* p) {
+    if (!STREAM) return *reinterpret_cast<const float4*>(p);
     const nt_f4 v = __builtin_nontemporal_load(reinterpret_cast<const nt_f4*>(p));
     return make_float4(v.x, v.y, v.z, v.w);
 }
-__device__ inline float2 nt_load2(const float* p) {
+template <bool STREAM>
+__device__ inline float2 row_load2(const float* p) {
+    if (!STREAM) return *reinterpret_cast<const float2*>(p);
     const nt_f2 v = __builtin_nontemporal_load(reinterpret_cast<const nt_f2*>(p));
     return make_float2(v.x, v.y);
 }
-__device__ inline void nt_store4(float* p, float4 v) { __builtin_nontemporal_store(nt_f4{v.x, v.y, v.z, v.w}, reinterpret_cast<nt_f4*>(p)); }
-__device__ inline void nt_store2(float* p, float2 v) { __builtin_nontemporal_store(nt_f2{v.x, v.y}, reinterpret_cast<nt_f2*>(p)); }
+// (The empty statements around a marked store keep the compiler from making one unmarked store of the two branches.)
+__device__ inline void row_store4(float* p, float4 v, int stream) {
+    const nt_f4 x = {v.x, v.y, v.z, v.w};
+    if (stream) {
+        asm volatile("");
+        __builtin_nontemporal_store(x, reinterpret_cast<nt_f4*>(p));
+        asm volatile("");
+    } else {
+        *reinterpret_cast<nt_f4*>(p) = x;
+    }
+}
+__device__ inline void row_store2(float* p, float2 v, int stream) {
+    const nt_f2 x = {v.x, v.y};
+    if (stream) {
+        asm volatile("");
+        __builtin_nontemporal_store(x, reinterpret_cast<nt_f2*>(p));
+        asm volatile("");
+    } else {
+        *reinterpret_cast<nt_f2*>(p) = x;
+    }
+}
+__device__ inline void row_store(float* p, float v, int stream) {
+    if (stream) {
+        asm volatile("");
+        __builtin_nontemporal_store(v, p);
+        asm volatile("");
+    } else {
+        *p = v;
+    }
+}
 
 }  // namespace legend

@@ -453,7 +453,8 @@ k_chunk(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, float
                 const int rt = w * 16 + s * RPS + grow_lane;
                 const int neg = n0 + rt;
                 if (neg < N && gc0 < d) {
-                    const int32_t id = neg < kIdsLds ? ids_s[neg] : my_negs[neg];
+                    typedef __attribute__((address_space(3))) const int32_t* lds_ids_t;     // as in gather_issue
+                    const int32_t id = neg < kIdsLds ? ((lds_ids_t)ids_s)[neg] : my_negs[neg];
                     const float* src = Ns + rt * QS + gc0;
                     float* dst = Gn + (int64_t)id * d + gc0;
                     unsafeAtomicAdd(dst, src[0]);
@@ -468,19 +469,18 @@ k_chunk(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, float
                 const int rt = w * 16 + s * RPS + grow_lane;
                 const int neg = n0 + rt;
                 if (neg < N && gc0 < d) {
-                    const float* src = Ns + rt * QS + gc0;
+                    const float4 v = lds4(Ns + rt * QS + gc0);
                     float* dst = grad + (neg_base + neg) * d + gc0;
                     if (vec4) {
-                        nt_store4(dst, lds4(src));
+                        row_store4(dst, v, bp.stream_rows);
                     } else if ((d & 1) == 0) {
-                        const float4 v = lds4(src);
-                        nt_store2(dst, make_float2(v.x, v.y));
-                        if (gc0 + 2 < d) nt_store2(dst + 2, make_float2(v.z, v.w));
+                        row_store2(dst, make_float2(v.x, v.y), bp.stream_rows);
+                        if (gc0 + 2 < d) row_store2(dst + 2, make_float2(v.z, v.w), bp.stream_rows);
                     } else {
-                        dst[0] = src[0];
-                        if (gc0 + 1 < d) dst[1] = src[1];
-                        if (gc0 + 2 < d) dst[2] = src[2];
-                        if (gc0 + 3 < d) dst[3] = src[3];
+                        dst[0] = v.x;
+                        if (gc0 + 1 < d) dst[1] = v.y;
+                        if (gc0 + 2 < d) dst[2] = v.z;
+                        if (gc0 + 3 < d) dst[3] = v.w;
                     }
                 }
             }

@@ -733,7 +733,7 @@ k_chunk_fast(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, 
                 const int k = idx / (d / 4);
                 const int n = neg_of(t, 16 * wl + k);
                 if (k < 16 && n < N)
-                    nt_store4(grad + (neg_base + n) * d + 4 * (idx - k * (d / 4)), lds4(St + 4 * idx));
+                    row_store4(grad + (neg_base + n) * d + 4 * (idx - k * (d / 4)), lds4(St + 4 * idx), bp.stream_rows);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();

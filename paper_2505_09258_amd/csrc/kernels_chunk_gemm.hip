@@ -558,7 +558,7 @@ k_gemm_gneg(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, c
                 const int n = n0 + 64 * wm + 16 * a + 4 * gq + v;
                 if (n >= N) continue;
                 if (atomic) unsafeAtomicAdd(Gn + (int64_t)my_negs[n] * d + col, acc[a][b][v]);
-                else __builtin_nontemporal_store(acc[a][b][v], grad + (neg_base + n) * d + col);
+                else row_store(grad + (neg_base + n) * d + col, acc[a][b][v], bp.stream_rows);
             }
         }
     }

@@ -31,16 +31,17 @@ __device__ inline int table_of_key(const UpdateTables& tb, uint32_t key) {
 }
 
 // Sum of gradient rows sorted_vals[lo..hi) (columns c0..c0+3) in that order, in fp64.
+template <bool STREAM>
 __device__ inline void sum_rows(const float* __restrict__ grad, const uint32_t* __restrict__ sorted_vals,
                                 uint32_t lo, uint32_t hi, int d, int c0, bool vec4, double acc[4]) {
     uint32_t p = lo;
     if (vec4) {
         for (; p + 4 <= hi; p += 4) {           // four independent loads in flight, added in order
             const uint32_t o0 = sorted_vals[p], o1 = sorted_vals[p + 1], o2 = sorted_vals[p + 2], o3 = sorted_vals[p + 3];
-            const float4 v0 = nt_load4(grad + (int64_t)o0 * d + c0);
-            const float4 v1 = nt_load4(grad + (int64_t)o1 * d + c0);
-            const float4 v2 = nt_load4(grad + (int64_t)o2 * d + c0);
-            const float4 v3 = nt_load4(grad + (int64_t)o3 * d + c0);
+            const float4 v0 = row_load4<STREAM>(grad + (int64_t)o0 * d + c0);
+            const float4 v1 = row_load4<STREAM>(grad + (int64_t)o1 * d + c0);
+            const float4 v2 = row_load4<STREAM>(grad + (int64_t)o2 * d + c0);
+            const float4 v3 = row_load4<STREAM>(grad + (int64_t)o3 * d + c0);
             acc[0] += (double)v0.x; acc[1] += (double)v0.y; acc[2] += (double)v0.z; acc[3] += (double)v0.w;
             acc[0] += (double)v1.x; acc[1] += (double)v1.y; acc[2] += (double)v1.z; acc[3] += (double)v1.w;
             acc[0] += (double)v2.x; acc[1] += (double)v2.y; acc[2] += (double)v2.z; acc[3] += (double)v2.w;
@@ -50,19 +51,19 @@ __device__ inline void sum_rows(const float* __restrict__ grad, const uint32_t* 
         // their loads go out together as well, the sums stay in order
         const uint32_t n = hi - p;
         if (n == 1) {
-            const float4 v0 = nt_load4(grad + (int64_t)sorted_vals[p] * d + c0);
+            const float4 v0 = row_load4<STREAM>(grad + (int64_t)sorted_vals[p] * d + c0);
             acc[0] += (double)v0.x; acc[1] += (double)v0.y; acc[2] += (double)v0.z; acc[3] += (double)v0.w;
         } else if (n == 2) {
             const uint32_t o0 = sorted_vals[p], o1 = sorted_vals[p + 1];
-            const float4 v0 = nt_load4(grad + (int64_t)o0 * d + c0);
-            const float4 v1 = nt_load4(grad + (int64_t)o1 * d + c0);
+            const float4 v0 = row_load4<STREAM>(grad + (int64_t)o0 * d + c0);
+            const float4 v1 = row_load4<STREAM>(grad + (int64_t)o1 * d + c0);
             acc[0] += (double)v0.x; acc[1] += (double)v0.y; acc[2] += (double)v0.z; acc[3] += (double)v0.w;
             acc[0] += (double)v1.x; acc[1] += (double)v1.y; acc[2] += (double)v1.z; acc[3] += (double)v1.w;
         } else if (n == 3) {
             const uint32_t o0 = sorted_vals[p], o1 = sorted_vals[p + 1], o2 = sorted_vals[p + 2];
-            const float4 v0 = nt_load4(grad + (int64_t)o0 * d + c0);
-            const float4 v1 = nt_load4(grad + (int64_t)o1 * d + c0);
-            const float4 v2 = nt_load4(grad + (int64_t)o2 * d + c0);
+            const float4 v0 = row_load4<STREAM>(grad + (int64_t)o0 * d + c0);
+            const float4 v1 = row_load4<STREAM>(grad + (int64_t)o1 * d + c0);
+            const float4 v2 = row_load4<STREAM>(grad + (int64_t)o2 * d + c0);
             acc[0] += (double)v0.x; acc[1] += (double)v0.y; acc[2] += (double)v0.z; acc[3] += (double)v0.w;
             acc[0] += (double)v1.x; acc[1] += (double)v1.y; acc[2] += (double)v1.z; acc[3] += (double)v1.w;
             acc[0] += (double)v2.x; acc[1] += (double)v2.y; acc[2] += (double)v2.z; acc[3] += (double)v2.w;
@@ -73,8 +74,8 @@ __device__ inline void sum_rows(const float* __restrict__ grad, const uint32_t* 
         const bool second = c0 + 2 < d;
         auto row2 = [&](uint32_t o, float2& a, float2& b) {
             const float* gp = grad + (int64_t)o * d + c0;
-            a = nt_load2(gp);
-            b = second ? nt_load2(gp + 2) : make_float2(0.f, 0.f);
+            a = row_load2<STREAM>(gp);
+            b = second ? row_load2<STREAM>(gp + 2) : make_float2(0.f, 0.f);
         };
         for (; p + 4 <= hi; p += 4) {
             float2 a0, b0, a1, b1, a2, b2, a3, b3;
@@ -155,7 +156,7 @@ k_long_list(uint32_t* __restrict__ counters, const uint32_t* __restrict__ seg_st
 
 // LPR lanes (a float4 each) own one table row: the rows u0, u0 + stride, ... of the batch's unique rows.
 // Rows with many gradient rows are left to the kernels below.
-template <int LPR>
+template <int LPR, bool STREAM>
 __device__ inline void update_short_rows(uint32_t u0, uint32_t stride, uint32_t n_unique,
                                          const uint32_t* __restrict__ uniq_keys, const uint32_t* __restrict__ seg_start,
                                          const uint32_t* __restrict__ sorted_vals, const float* __restrict__ grad,
@@ -178,7 +179,7 @@ __device__ inline void update_short_rows(uint32_t u0, uint32_t stride, uint32_t 
                 float4 th = *reinterpret_cast<const float4*>(ep);
                 float4 st = *reinterpret_cast<const float4*>(sp);
                 double acc[4] = {0.0, 0.0, 0.0, 0.0};
-                sum_rows(grad, sorted_vals, lo, hi, d, c0, true, acc);
+                sum_rows<STREAM>(grad, sorted_vals, lo, hi, d, c0, true, acc);
                 adagrad_elem((float)acc[0], th.x, st.x, lr, eps);
                 adagrad_elem((float)acc[1], th.y, st.y, lr, eps);
                 adagrad_elem((float)acc[2], th.z, st.z, lr, eps);
@@ -190,19 +191,19 @@ __device__ inline void update_short_rows(uint32_t u0, uint32_t stride, uint32_t 
         }
         for (int cc = c0; cc < d; cc += 4 * LPR) {     // rows wider than 4*LPR floats take several passes
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            sum_rows(grad, sorted_vals, lo, hi, d, cc, vec4, acc);
+            sum_rows<STREAM>(grad, sorted_vals, lo, hi, d, cc, vec4, acc);
             apply_row(tb, uniq_keys[u], acc, d, cc, vec4, lr, eps);
         }
     }
 }
 
-template <int LPR>
+template <int LPR, bool STREAM>
 __global__ void __launch_bounds__(256)
 k_update(const uint32_t* __restrict__ counters, const uint32_t* __restrict__ uniq_keys,
          const uint32_t* __restrict__ seg_start, const uint32_t* __restrict__ sorted_vals,
          const float* __restrict__ grad, UpdateTables tb, int d, float lr, float eps) {
     constexpr int groups_per_block = 256 / LPR;
-    update_short_rows<LPR>(blockIdx.x * groups_per_block + threadIdx.x / LPR, gridDim.x * groups_per_block, counters[0],
+    update_short_rows<LPR, STREAM>(blockIdx.x * groups_per_block + threadIdx.x / LPR, gridDim.x * groups_per_block, counters[0],
                            uniq_keys, seg_start, sorted_vals, grad, tb, d, lr, eps);
 }
 
@@ -246,7 +247,7 @@ k_long_plan(uint32_t* __restrict__ counters, const uint32_t* __restrict__ long_l
 
 // One block per unit: the block's groups sum kUnit / GROUPS consecutive gradient rows each, the partial
 // sums are added in group order by the lanes of group 0, which get the unit's fp64 sum of columns cc..cc+3.
-template <int LPR>
+template <int LPR, bool STREAM>
 __device__ inline void unit_sum(uint32_t lo_unit, uint32_t seg_hi, const uint32_t* __restrict__ sorted_vals,
                                 const float* __restrict__ grad, int d, int cbase, bool vec4, double* psum, double tot[4]) {
     constexpr int GROUPS = 256 / LPR;
@@ -257,7 +258,7 @@ __device__ inline void unit_sum(uint32_t lo_unit, uint32_t seg_hi, const uint32_
     const uint32_t lo = lo_unit + gl * PER_GROUP;
     const uint32_t hi = min(seg_hi, lo + PER_GROUP);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (cc < d && lo < hi) sum_rows(grad, sorted_vals, lo, hi, d, cc, vec4, acc);
+    if (cc < d && lo < hi) sum_rows<STREAM>(grad, sorted_vals, lo, hi, d, cc, vec4, acc);
 #pragma unroll
     for (int j = 0; j < 4; ++j) psum[(gl * LPR + col4) * 4 + j] = acc[j];
     __syncthreads();
@@ -271,7 +272,7 @@ __device__ inline void unit_sum(uint32_t lo_unit, uint32_t seg_hi, const uint32_
     __syncthreads();
 }
 
-template <int LPR>
+template <int LPR, bool STREAM>
 __global__ void __launch_bounds__(256)
 k_long_partial(const uint32_t* __restrict__ counters, const uint32_t* __restrict__ long_list,
                const uint32_t* __restrict__ unit_start, const uint32_t* __restrict__ seg_start,
@@ -293,7 +294,7 @@ k_long_partial(const uint32_t* __restrict__ counters, const uint32_t* __restrict
         for (int cbase = 0; cbase < d; cbase += 4 * LPR) {     // uniform trip count across the block
             const int cc = cbase + col4 * 4;
             double tot[4];
-            unit_sum<LPR>(seg_lo + (unit - unit_start[a]) * kUnit, seg_hi, sorted_vals, grad, d, cbase, vec4, psum, tot);
+            unit_sum<LPR, STREAM>(seg_lo + (unit - unit_start[a]) * kUnit, seg_hi, sorted_vals, grad, d, cbase, vec4, psum, tot);
             if (gl == 0 && cc < d)
                 for (int j = 0; j < 4 && cc + j < d; ++j) partial[(int64_t)unit * d + cc + j] = tot[j];
         }
@@ -357,7 +358,7 @@ k_update_small(const uint32_t* __restrict__ counters, const uint32_t* __restrict
     constexpr int groups_per_block = 256 / LPR;
     const int b = blockIdx.x;
     if (b < row_blocks) {
-        update_short_rows<LPR>(b * groups_per_block + threadIdx.x / LPR, row_blocks * groups_per_block, counters[0],
+        update_short_rows<LPR, false>(b * groups_per_block + threadIdx.x / LPR, row_blocks * groups_per_block, counters[0],
                                uniq_keys, seg_start, sorted_vals, grad, tb, d, lr, eps);
         return;
     }
@@ -384,7 +385,7 @@ k_update_small(const uint32_t* __restrict__ counters, const uint32_t* __restrict
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         for (uint32_t lo = seg_lo; lo < seg_hi; lo += kUnit) {
             double tot[4];
-            unit_sum<LPR>(lo, seg_hi, sorted_vals, grad, d, cbase, vec4, psum, tot);
+            unit_sum<LPR, false>(lo, seg_hi, sorted_vals, grad, d, cbase, vec4, psum, tot);
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[j] += tot[j];
         }
@@ -392,7 +393,7 @@ k_update_small(const uint32_t* __restrict__ counters, const uint32_t* __restrict
     }
 }
 
-template <int LPR>
+template <int LPR, bool STREAM>
 static hipError_t launch_update_lpr(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws,
                                     const uint32_t* sorted_vals, const UpdateTables& tb, bool long_rows) {
     const int d = bp.dim;
@@ -400,13 +401,13 @@ static hipError_t launch_update_lpr(hipStream_t st, const BatchGeom& g, const Bu
     if (!long_rows) {
         int64_t blocks = (g.n_occ + groups - 1) / groups;
         if (blocks > 8192) blocks = 8192;
-        hipLaunchKernelGGL(k_update<LPR>, dim3((unsigned)blocks), dim3(256), 0, st, ws.counters, ws.uniq_keys, ws.seg_start,
+        hipLaunchKernelGGL((k_update<LPR, STREAM>), dim3((unsigned)blocks), dim3(256), 0, st, ws.counters, ws.uniq_keys, ws.seg_start,
                            sorted_vals, ws.grad, tb, d, bp.lr, bp.eps);
         return hipGetLastError();
     }
     int64_t max_units = g.n_occ / kUnit + g.n_occ / (kLongLen + 1) + 1;
     int64_t ublocks = max_units < 2048 ? max_units : 2048;
-    hipLaunchKernelGGL(k_long_partial<LPR>, dim3((unsigned)ublocks), dim3(256), sizeof(double) * 4 * 256, st, ws.counters,
+    hipLaunchKernelGGL((k_long_partial<LPR, STREAM>), dim3((unsigned)ublocks), dim3(256), sizeof(double) * 4 * 256, st, ws.counters,
                        ws.long_list, ws.unit_start, ws.seg_start, sorted_vals, ws.grad, d, ws.long_partial);
     int64_t fblocks = (g.n_occ / (kLongLen + 1) + groups) / groups;
     if (fblocks > 1024) fblocks = 1024;
@@ -439,10 +440,10 @@ hipError_t launch_update(hipStream_t st, const BatchGeom& g, const BucketParams&
     tb.E[2] = bp.E_rel; tb.S[2] = bp.S_rel;
     tb.key_base[0] = 0; tb.key_base[1] = bp.key_base_dst; tb.key_base[2] = bp.key_base_rel;
     const int d = bp.dim;
-    if (d <= 32) return launch_update_lpr<8>(st, g, bp, ws, sorted_vals, tb, long_rows);
-    if (d <= 64) return launch_update_lpr<16>(st, g, bp, ws, sorted_vals, tb, long_rows);
-    if (d <= 128) return launch_update_lpr<32>(st, g, bp, ws, sorted_vals, tb, long_rows);
-    return launch_update_lpr<64>(st, g, bp, ws, sorted_vals, tb, long_rows);
+    if (d <= 32) return (bp.stream_rows ? launch_update_lpr<8, true> : launch_update_lpr<8, false>)(st, g, bp, ws, sorted_vals, tb, long_rows);
+    if (d <= 64) return (bp.stream_rows ? launch_update_lpr<16, true> : launch_update_lpr<16, false>)(st, g, bp, ws, sorted_vals, tb, long_rows);
+    if (d <= 128) return (bp.stream_rows ? launch_update_lpr<32, true> : launch_update_lpr<32, false>)(st, g, bp, ws, sorted_vals, tb, long_rows);
+    return (bp.stream_rows ? launch_update_lpr<64, true> : launch_update_lpr<64, false>)(st, g, bp, ws, sorted_vals, tb, long_rows);
 }
 
 template <int LPR>

@@ -86,6 +86,7 @@ struct BucketParams {
     uint32_t key_base_dst;     // key offset of table slot 1 (0 when same_part)
     uint32_t key_base_rel;     // key offset of the relation table
     int32_t num_degree_negs;
+    int32_t stream_rows;       // mark gradient rows as streaming
     float lr, eps, neg_weight;
     float margin;              // margin loss: a negative should score this much below its positive
     uint64_t hash_prefix;      // hash state after (seed, epoch, i, j, b)

@@ -133,6 +133,7 @@ struct legend_ctx {
     int64_t prof_launches[KC_COUNT] = {0};
     int64_t batches_done = 0;
     bool index_after_chunk = false;         // LEGEND_INDEX_AFTER_CHUNK=1: the next batch's index side starts when this batch's chunk kernel has finished, not when it is launched (a measurement knob)
+    int32_t stream_rows = -1;               // LEGEND_STREAM_ROWS=0 or 1: never or always (tests compare the two); else streams_rows decides
     bool no_small_update = false;           // LEGEND_NO_SMALL_UPDATE=1: small batches take the general update kernels too (tests compare the two)
     bool serial_sort = false;               // LEGEND_SERIAL_SORT=1: everything on the compute stream, batch after batch (for per-kernel timing)
     bool keep_loss = false;                 // epoch driver: do not reset the device loss sum per bucket
@@ -414,6 +415,21 @@ int stage_edges(legend_ctx* c, int i, int j, const int32_t* edges, int64_t m, in
     return LEGEND_OK;
 }
 
+// Are a batch's gradient rows marked as streaming?  They are where the rows, the bucket's tables and the wide path's buffers
+// exceed the 256 MB of the Infinity Cache together: then the rows of a batch would throw out the tables of the next.  Where
+// everything fits, the marks send the rows past a cache that would have held them.  A batch's time with marks against without,
+// by total: d = 100, 99 to 214 MB 1 to 4 % more, 252 MB 1 % more, 290 MB 1 % less, 443 MB (1M rows of tables and more: 1.2 GB) 2 %
+// (3 %) less; d = 64, 208 MB 1 % more, 256 MB 4 % less, 354 MB 6 % less; d = 50 (200-byte rows), 56 MB 4 % and 182 MB
+// 5 % more, 269 MB 1 % less; wide path d = 400, 158 MB 1 % more, 267 MB 2 %, 320 MB 4 %, 480 MB 8 % less.
+int32_t streams_rows(const legend_ctx* c, int i, int j, int64_t m) {
+    constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+    const BatchGeom g = make_geom(c, (int)std::min<int64_t>(m, c->cfg.batch_size));
+    const int64_t table_rows = rows_valid(c, i) + (i != j ? rows_valid(c, j) : 0) + (c->uses_rel ? c->nrel_rows : 0);
+    int64_t floats = (g.n_occ + 2 * table_rows) * c->d;                        // embeddings and states
+    if (c->d > 128) floats += (int64_t)g.sides * g.P * (2 * c->d + gemm_npad(g.N));       // Q, its gradient, scores
+    return floats * (int64_t)sizeof(float) > kCacheBytes;
+}
+
 int bucket_params(legend_ctx* c, int i, int j, const int32_t* dev_edges, int64_t m, BucketParams* bp) {
     int si = c->part_slot[i], sj = c->part_slot[j];
     if (si < 0 || sj < 0) return fail(LEGEND_E_NOT_RESIDENT, "bucket (%d,%d): partition %d is not resident", i, j, si < 0 ? i : j);
@@ -443,6 +459,7 @@ int bucket_params(legend_ctx* c, int i, int j, const int32_t* dev_edges, int64_t
     p.key_base_dst = i == j ? 0u : (uint32_t)c->Rp;
     p.key_base_rel = i == j ? (uint32_t)c->Rp : (uint32_t)(2 * c->Rp);
     p.num_degree_negs = c->cfg.num_degree_negs;
+    p.stream_rows = c->stream_rows >= 0 ? c->stream_rows : streams_rows(c, i, j, m);
     p.lr = c->cfg.lr;
     p.eps = c->cfg.eps;
     p.neg_weight = c->cfg.neg_weight >= 0.f ? c->cfg.neg_weight : 1.0f / (float)c->cfg.num_negs;
@@ -542,6 +559,8 @@ int legend_init_partitions(const legend_config* cfg, const float* init_node_emb,
         c->index_after_chunk = wc && wc[0] == '1';
         const char* ns = std::getenv("LEGEND_NO_SMALL_UPDATE");
         c->no_small_update = ns && ns[0] == '1';
+        const char* sr = std::getenv("LEGEND_STREAM_ROWS");
+        c->stream_rows = sr && (sr[0] == '0' || sr[0] == '1') ? sr[0] - '0' : -1;
     }
     c->nrel_rows = std::max(cfg->num_relations, 1);
     c->host_part.assign(c->n, nullptr);
