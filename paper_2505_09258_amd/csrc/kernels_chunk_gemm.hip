@@ -35,13 +35,19 @@ static_assert(kGRows == kWideRowTile, "tile geometry");
 
 // Elements k..k+7 of a row of d; elements past its end are others of the row (loads only: what is done to a loaded value
 // at once waits for it).
-template <bool VEC>                           // rows are 16-byte aligned (d a multiple of four)
+template <int LW>                            // floats per load: 4 where d is a multiple of four (rows are 16-byte aligned), 2 where it is even, 1
 __device__ inline void load8(const float* __restrict__ row, int k, int d, float (&v)[8]) {
-    if (VEC) {
+    if (LW == 4) {
         const float4 a = *reinterpret_cast<const float4*>(row + (k < d ? k : 0));
         const float4 b = *reinterpret_cast<const float4*>(row + (k + 4 < d ? k + 4 : 0));
         v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
         v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    } else if (LW == 2) {
+#pragma unroll
+        for (int t = 0; t < 8; t += 2) {
+            const float2 a = *reinterpret_cast<const float2*>(row + (k + t < d ? k + t : 0));
+            v[t] = a.x; v[t + 1] = a.y;
+        }
     } else {
 #pragma unroll
         for (int t = 0; t < 8; ++t) v[t] = row[min(k + t, d - 1)];
@@ -169,9 +175,10 @@ k_gemm_compose(BatchGeom g, BucketParams bp, float* __restrict__ Q, float* __res
 // grid: (tiles of 128 negatives, row tiles).  Four waves; wave w owns negatives 32w..32w+31 of the tile
 // and all row blocks.  S is stored as [row tile][64-negative tile][row][64], so that the tiles the
 // later kernels load are contiguous.
-// VEC is a template parameter because the compiler made one loop of 32-bit loads of the two branches (four times the load
-// instructions: 217 us a batch of the shape below, more than the matrix work took before).
-template <int RB, bool VEC>                   // row blocks of 16 that the tile geometry needs; d a multiple of four
+// The load width is a template parameter because the compiler made one loop of 32-bit loads of the branches (four times the load
+// instructions: 217 us a batch of the shape above, more than the matrix work took before).  An even d that is no multiple of four (150
+// of the dimension sweep) has its 64-bit loads: 5 000 edges, 1000 negatives, d = 150 319 -> 255 us a batch, d = 510 614 -> 550.
+template <int RB, int LW>                     // row blocks of 16 that the tile geometry needs; floats per load
 __global__ void __launch_bounds__(kGThreads, 3)
 k_gemm_scores(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, const float* __restrict__ Q,
               float* __restrict__ S, int Npad, int nx, int64_t ny) {
@@ -204,9 +211,9 @@ k_gemm_scores(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     float qv[QI][8], nv[2][8];
     auto fetch = [&](int c0) {
 #pragma unroll
-        for (int u = 0; u < QI; ++u) load8<VEC>(qrow[u], c0 + 8 * kg, d, qv[u]);
+        for (int u = 0; u < QI; ++u) load8<LW>(qrow[u], c0 + 8 * kg, d, qv[u]);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) load8<VEC>(nrow[u], c0 + 8 * kg, d, nv[u]);
+        for (int u = 0; u < 2; ++u) load8<LW>(nrow[u], c0 + 8 * kg, d, nv[u]);
     };
     f32v4 acc[RB][2];
 #pragma unroll
@@ -414,7 +421,7 @@ k_gemm_gq(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, con
     auto fetch = [&](int n0) {
         const int64_t off = (int64_t)(n0 >> 6) * tile_stride + (n0 & 63) + 8 * kg;
 #pragma unroll
-        for (int u = 0; u < WI; ++u) load8<true>(wrow[u] + off, 0, 8, wv[u]);
+        for (int u = 0; u < WI; ++u) load8<4>(wrow[u] + off, 0, 8, wv[u]);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -650,7 +657,7 @@ hipError_t launch_chunks_gemm(hipStream_t st, const BatchGeom& g, const BucketPa
     const int rb = (g.rows_tile + 15) / 16;
 #define LEGEND_GEMM_RB(RB)                                                                                             \
     case RB: {                                                                                                         \
-        auto scores = bp.dim % 4 == 0 ? k_gemm_scores<RB, true> : k_gemm_scores<RB, false>;                            \
+        auto scores = bp.dim % 4 == 0 ? k_gemm_scores<RB, 4> : bp.dim % 2 == 0 ? k_gemm_scores<RB, 2> : k_gemm_scores<RB, 1>; \
         hipLaunchKernelGGL(scores, dim3((unsigned)xcd_grid(ntiles * tiles)), dim3(kGThreads), 0, st, g, bp, ws.neg_ids, \
                            ws.gemm_Q, ws.gemm_S, Npad, ntiles, tiles);                                                 \
         break;                                                                                                         \

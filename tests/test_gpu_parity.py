@@ -92,6 +92,15 @@ _WIDE_EDGES = [
     _case("distmult_d388_n257_rows33", DISTMULT, SOFTMAX, DST, 900, 3, 388, 1, 0, 0, 66, 33, 257, 0, 140, 0.15),
 ]
 
+# The same with so many workgroups (512 tiles of 128 negatives, and of 128 x 128 of their gradients, and more) that the tiles are full-sized,
+# at rows of 16, 8 and 4 bytes' alignment.
+_WIDE_MANY = [
+    _case("complex_d130_n129_rows112", COMPLEX, SOFTMAX, BOTH, 4_000, 3, 130, 1, 0, 0, 14_336, 112, 129, 0, 14_500, 0.2),
+    _case("distmult_d160_n257_rows33", DISTMULT, LOGISTIC, BOTH, 3_000, 3, 160, 2, 0, 1, 2_838, 33, 257, 9, 2_900, 0.2),
+    _case("dot_d255_n500_rows50", DOT, SOFTMAX, DST, 3_000, 0, 255, 1, 0, 0, 6_400, 50, 500, 0, 6_410, 0.2),
+    _case("dot_d150_n128_rows16", DOT, MARGIN, SRC, 3_000, 0, 150, 1, 0, 0, 8_192, 16, 128, 0, 8_200, 0.2),
+]
+
 # One node row in 64 is four times larger than the rest, so that some chunks hold a score far
 # above the positive's and others do not.
 _HOT_CASE = dict(_case("dot_d100_hot_rows", DOT, SOFTMAX, DST, 12_000, 0, 100, 2, 0, 1, 1_000, 50, 300, 0, 2_500, 0.1),
@@ -183,6 +192,11 @@ def test_translational_kernel_at_its_edges(c):
 
 @pytest.mark.parametrize("c", _WIDE_EDGES, ids=[c["name"] for c in _WIDE_EDGES])
 def test_wide_path_at_its_tile_edges(c):
+    _check_every_batch(c)
+
+
+@pytest.mark.parametrize("c", _WIDE_MANY, ids=[c["name"] for c in _WIDE_MANY])
+def test_wide_path_with_many_workgroups(c):
     _check_every_batch(c)
 
 
