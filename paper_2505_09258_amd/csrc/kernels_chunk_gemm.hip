@@ -12,7 +12,7 @@
 // The contractions were bound by the fp32 matrix pipe and the LDS reads that feed it (58 to 75 TFLOP/s of 139).  Now every
 // operand is cut into three bf16 parts on its way into LDS, as fp32 products of six bf16 instructions (split_bf16.h), and
 // read back as the eight contraction elements of a lane, one 128-bit read per part.  All three work on slices of 32
-// contraction elements with 128 columns or negatives to a tile, the next slice on its way from memory; about 50 KB of
+// contraction elements with 128 (small batches: 64) columns or negatives to a tile, the next slice on its way from memory; about 50 KB of
 // LDS and at most 168 registers leave three workgroups to a compute unit, which cut and multiply in turn.  An operand whose contraction
 // index is the slow one in memory is loaded by one thread per column, eight rows each: whole lines per instruction.
 // Measured on batches of 10 000 edges, both sides, 1000 negatives, d = 400 (200 row tiles of 100): G_Q 276 -> 161 us, G_neg 255 ->
@@ -30,6 +30,14 @@ constexpr int kGNeg = 64;                // negatives per tile of the score buff
 constexpr int kGTile = 128;              // negatives or columns per workgroup
 constexpr int kGK = 32;                  // contraction elements per slice
 constexpr int kGThreads = 256;
+// Below this many workgroups (two to a compute unit) the scores and G_neg kernels take tiles of 64 negatives instead of 128:
+// a small batch is bound by the latency of its slices, one after the other in every workgroup, and by columns of negatives
+// that do not exist.  A batch at d = 400 (start of the work on split products: fp32 tiles of 64), with tiles of 128, with 64, in us:
+//   1000 edges, both sides, 100 negatives, 20 tiles of scores    130, 136, 126
+//   2000 edges, both sides,  64 negatives, 40 tiles              139, 147, 139
+//   5000 edges, 1000 negatives, 800 tiles                        428, 337, 346
+// The two cross between 400 and 800 workgroups of either kernel (d = 130 to 512; at 1600 tiles of 64 cost 3 to 8 %).
+constexpr int kGFew = 512;
 
 static_assert(kGRows == kWideRowTile, "tile geometry");
 
@@ -65,28 +73,33 @@ __device__ inline bool any_nan(f32v4 x) {
     return s != s;
 }
 
-// acc[a][b] += A_a B_b^T of one slice for RA blocks of 16 rows (of which two at a time are in registers) and two blocks
+// acc[a][b] += A_a B_b^T of one slice for RA blocks of 16 rows (of which two at a time are in registers) and NB blocks
 // of 16 columns
-template <int RA, class TA, class TB>
-__device__ __forceinline__ void slice_mfma(const char* As, const char* Bs, int col0, int l15, int gq, f32v4 (&acc)[RA][2]) {
-    Split8 B[2];
+template <int RA, int NB, class TA, class TB>
+__device__ __forceinline__ void slice_mfma(const char* As, const char* Bs, int col0, int l15, int gq, f32v4 (&acc)[RA][NB]) {
+    Split8 B[NB];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) B[b] = TB::load(Bs, col0 + 16 * b + l15, gq);
+    for (int b = 0; b < NB; ++b) B[b] = TB::load(Bs, col0 + 16 * b + l15, gq);
 #pragma unroll
     for (int a = 0; a + 1 < RA; a += 2) {
         Split8 A[2];
         A[0] = TA::load(As, 16 * a + l15, gq);
         A[1] = TA::load(As, 16 * a + 16 + l15, gq);
-        f32v4 c[2][2] = {{acc[a][0], acc[a][1]}, {acc[a + 1][0], acc[a + 1][1]}};
+        f32v4 c[2][NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) { c[0][b] = acc[a][b]; c[1][b] = acc[a + 1][b]; }
         split_mfma(A, B, c);
-        acc[a][0] = c[0][0]; acc[a][1] = c[0][1];
-        acc[a + 1][0] = c[1][0]; acc[a + 1][1] = c[1][1];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) { acc[a][b] = c[0][b]; acc[a + 1][b] = c[1][b]; }
     }
     if constexpr (RA % 2 == 1) {
         Split8 A[1] = {TA::load(As, 16 * (RA - 1) + l15, gq)};
-        f32v4 c[1][2] = {{acc[RA - 1][0], acc[RA - 1][1]}};
+        f32v4 c[1][NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) c[0][b] = acc[RA - 1][b];
         split_mfma(A, B, c);
-        acc[RA - 1][0] = c[0][0]; acc[RA - 1][1] = c[0][1];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[RA - 1][b] = c[0][b];
     }
 }
 
@@ -172,18 +185,20 @@ k_gemm_compose(BatchGeom g, BucketParams bp, float* __restrict__ Q, float* __res
 }
 
 // ---- S = Q Neg^T ---------------------------------------------------------------------------------
-// grid: (tiles of 128 negatives, row tiles).  Four waves; wave w owns negatives 32w..32w+31 of the tile
+// grid: (tiles of 64 NB negatives, row tiles).  Four waves; wave w owns the 16 NB negatives from 16 NB w of the tile
 // and all row blocks.  S is stored as [row tile][64-negative tile][row][64], so that the tiles the
 // later kernels load are contiguous.
 // The load width is a template parameter because the compiler made one loop of 32-bit loads of the branches (four times the load
 // instructions: 217 us a batch of the shape above, more than the matrix work took before).  An even d that is no multiple of four (150
 // of the dimension sweep) has its 64-bit loads: 5 000 edges, 1000 negatives, d = 150 319 -> 255 us a batch, d = 510 614 -> 550.
-template <int RB, int LW>                     // row blocks of 16 that the tile geometry needs; floats per load
+// NB = 1 is for batches with few workgroups (kGFew): twice as many, and two slices on their way instead of one, since
+// nothing else on the compute unit covers their latency.
+template <int RB, int LW, int NB>             // row blocks of 16 that the tile geometry needs; floats per load; 64-negative blocks
 __global__ void __launch_bounds__(kGThreads, 3)
 k_gemm_scores(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, const float* __restrict__ Q,
               float* __restrict__ S, int Npad, int nx, int64_t ny) {
     using QTile = SplitTile<16 * RB>;
-    using NTile = SplitTile<kGTile>;
+    using NTile = SplitTile<64 * NB>;
     __shared__ __align__(16) char Qs[QTile::BYTES];
     __shared__ __align__(16) char Ns[NTile::BYTES];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l15 = lane & 15, gq = lane >> 4;
@@ -192,7 +207,7 @@ k_gemm_scores(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     if (!xcd_tile((int64_t)nx * ny, nx, &bx, &by)) return;       // uniform
     const TileCoord tc = tile_coord(g, by);
     if (tc.nrows == 0) return;                // uniform: no scores, and nobody reads any
-    const int n0 = bx * kGTile;
+    const int n0 = bx * 64 * NB;
     const int N = g.N, d = bp.dim;
     const float* En = tc.side == 0 ? bp.E_dst : bp.E_src;
     const float* Qrows = Q + ((int64_t)tc.si * g.P + tc.e0) * d;
@@ -202,52 +217,61 @@ k_gemm_scores(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     // not exist are replaced by the last one, and their scores are not written
     const int srow = tid >> 2, kg = tid & 3;
     constexpr int QI = (RB + 3) / 4;
+    constexpr int AHEAD = NB == 1 ? 2 : 1;    // slices on their way
     const float* qrow[QI];
-    const float* nrow[2];
+    const float* nrow[NB];
 #pragma unroll
     for (int u = 0; u < QI; ++u) qrow[u] = Qrows + (int64_t)min(srow + 64 * u, tc.nrows - 1) * d;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) nrow[u] = En + (int64_t)my_negs[min(n0 + srow + 64 * u, N - 1)] * d;
-    float qv[QI][8], nv[2][8];
-    auto fetch = [&](int c0) {
+    for (int u = 0; u < NB; ++u) nrow[u] = En + (int64_t)my_negs[min(n0 + srow + 64 * u, N - 1)] * d;
+    float qv[AHEAD][QI][8], nv[AHEAD][NB][8];
+    auto fetch = [&](int s, int c0) {
 #pragma unroll
-        for (int u = 0; u < QI; ++u) load8<LW>(qrow[u], c0 + 8 * kg, d, qv[u]);
+        for (int u = 0; u < QI; ++u) load8<LW>(qrow[u], c0 + 8 * kg, d, qv[s][u]);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) load8<LW>(nrow[u], c0 + 8 * kg, d, nv[u]);
+        for (int u = 0; u < NB; ++u) load8<LW>(nrow[u], c0 + 8 * kg, d, nv[s][u]);
     };
-    f32v4 acc[RB][2];
+    f32v4 acc[RB][NB];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) acc[r][0] = acc[r][1] = f32v4{0.f, 0.f, 0.f, 0.f};
-    fetch(0);
-    for (int c0 = 0; c0 < d; c0 += kGK) {
-        if (c0 + kGK > d) {                   // components past the end
+    for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int u = 0; u < QI; ++u) zero_past(qv[u], c0 + 8 * kg, d);
+        for (int b = 0; b < NB; ++b) acc[r][b] = f32v4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < 2; ++u) zero_past(nv[u], c0 + 8 * kg, d);
+    for (int s = 0; s < AHEAD; ++s) fetch(s, kGK * s);
+    for (int cs = 0; cs < d; cs += kGK * AHEAD) {
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) {
+            const int c0 = cs + kGK * s;
+            if (c0 >= d) break;               // uniform
+            if (c0 + kGK > d) {               // components past the end
+#pragma unroll
+                for (int u = 0; u < QI; ++u) zero_past(qv[s][u], c0 + 8 * kg, d);
+#pragma unroll
+                for (int u = 0; u < NB; ++u) zero_past(nv[s][u], c0 + 8 * kg, d);
+            }
+#pragma unroll
+            for (int u = 0; u < QI; ++u)
+                if (srow + 64 * u < 16 * RB) QTile::store(Qs, srow + 64 * u, kg, split8(qv[s][u]));
+#pragma unroll
+            for (int u = 0; u < NB; ++u) NTile::store(Ns, srow + 64 * u, kg, split8(nv[s][u]));
+            __syncthreads();
+            if (c0 + kGK * AHEAD < d) fetch(s, c0 + kGK * AHEAD);
+            slice_mfma<RB, NB, QTile, NTile>(Qs, Ns, 16 * NB * w, l15, gq, acc);
+            __syncthreads();
         }
-#pragma unroll
-        for (int u = 0; u < QI; ++u)
-            if (srow + 64 * u < 16 * RB) QTile::store(Qs, srow + 64 * u, kg, split8(qv[u]));
-#pragma unroll
-        for (int u = 0; u < 2; ++u) NTile::store(Ns, srow + 64 * u, kg, split8(nv[u]));
-        __syncthreads();
-        if (c0 + kGK < d) fetch(c0 + kGK);
-        slice_mfma<RB, QTile, NTile>(Qs, Ns, 32 * w, l15, gq, acc);
-        __syncthreads();
     }
     bool nan = false;                         // an infinity took part, or the score is a NaN
 #pragma unroll
     for (int r = 0; r < RB; ++r)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) nan |= any_nan(acc[r][b]);
+        for (int b = 0; b < NB; ++b) nan |= any_nan(acc[r][b]);
     if (__builtin_expect(__any(nan), 0))
         plain_products(d, [&](int r, int k) { return Qrows[(int64_t)min(16 * r + l15, tc.nrows - 1) * d + k]; },
-                       [&](int b, int k) { return En[(int64_t)my_negs[min(n0 + 32 * w + 16 * b + l15, N - 1)] * d + k]; }, acc);
+                       [&](int b, int k) { return En[(int64_t)my_negs[min(n0 + 16 * NB * w + 16 * b + l15, N - 1)] * d + k]; }, acc);
     float* Srow = S + (int64_t)tc.wgrow * g.rows_tile * Npad;
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int n = n0 + 32 * w + 16 * b + l15;
+    for (int b = 0; b < NB; ++b) {
+        const int n = n0 + 16 * NB * w + 16 * b + l15;
         if (n >= N) continue;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
@@ -441,7 +465,7 @@ k_gemm_gq(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, con
         for (int u = 0; u < 2; ++u) NTile::store(Ns, tid & 127, kgc + 2 * u, split8(nv[u]));
         __syncthreads();
         if (n0 + kGK < N) fetch(n0 + kGK);
-        if (live) slice_mfma<RB, WTile, NTile>(Ws, Ns, 32 * w, l15, gq, acc);
+        if (live) slice_mfma<RB, 2, WTile, NTile>(Ws, Ns, 32 * w, l15, gq, acc);
         __syncthreads();
     }
     bool nan = false;
@@ -469,21 +493,25 @@ k_gemm_gq(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, con
 }
 
 // ---- G_neg = W^T Q -------------------------------------------------------------------------------
-// grid: (tiles of 128 columns x tiles of 128 negatives, row tiles).  The positives are the contraction index: both operands
-// are loaded eight rows of one column (or negative) to a thread.  Wave (wm, wn) owns 64 negatives x 64 columns.
+// grid: (tiles of 128 columns x tiles of 32 MB negatives, row tiles).  The positives are the contraction index: both operands
+// are loaded eight rows of one column (or negative) to a thread.  Wave (wm, wn) owns 16 MB negatives x 64 columns.
+// MB = 2 is for batches with few workgroups, as in the scores kernel (kGFew).
+template <int MB>
 __global__ void __launch_bounds__(kGThreads, 3)
 k_gemm_gneg(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, const float* __restrict__ W, int Npad,
             const float* __restrict__ Q, float* __restrict__ grad, int ncol, int nx, int64_t ny) {
-    using Tile = SplitTile<kGTile>;
-    __shared__ __align__(16) char Ws[Tile::BYTES];
-    __shared__ __align__(16) char Qs[Tile::BYTES];
+    constexpr int NEGS = 32 * MB, WU = MB / 2;
+    using WTile = SplitTile<NEGS>;
+    using QTile = SplitTile<kGTile>;
+    __shared__ __align__(16) char Ws[WTile::BYTES];
+    __shared__ __align__(16) char Qs[QTile::BYTES];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l15 = lane & 15, gq = lane >> 4;
     const int wm = w >> 1, wn = w & 1;
     int bx;
     int64_t by;
     if (!xcd_tile((int64_t)nx * ny, nx, &bx, &by)) return;       // uniform
     const TileCoord tc = tile_coord(g, by);
-    const int c0 = bx % ncol * kGTile, n0 = bx / ncol * kGTile;
+    const int c0 = bx % ncol * kGTile, n0 = bx / ncol * NEGS;
     const int N = g.N, d = bp.dim, nrows = tc.nrows;
     const int32_t* my_negs = neg_ids + ((int64_t)tc.si * g.nchunks + tc.c) * N;
     const float* Wtile = W + (int64_t)tc.wgrow * g.rows_tile * Npad;
@@ -492,82 +520,110 @@ k_gemm_gneg(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, c
     float* Gn = tc.side == 0 ? bp.G_dst : bp.G_src;
     const int64_t neg_base = (int64_t)tc.si * g.per_side + (int64_t)g.roles * g.P + ((int64_t)tc.c * g.T + tc.t_row) * N;
 
-    const int wcol = min(n0 + (tid & 127), Npad - 1);
+    const int wcol = min(n0 + tid % NEGS, Npad - 1);
     const float* wp = Wtile + (int64_t)(wcol >> 6) * g.rows_tile * kGNeg + (wcol & 63);
     const float* qp = Qrows + min(c0 + (tid & 127), d - 1);
-    const int kgc = __builtin_amdgcn_readfirstlane(tid >> 7);
-    float wv[2][8], qv[2][8];
-    auto fetch = [&](int r0) {                // rows past the last one are replaced by it and get weight zero below
+    const int kgq = __builtin_amdgcn_readfirstlane(tid >> 7), kgw = __builtin_amdgcn_readfirstlane(tid / NEGS);
+    constexpr int AHEAD = MB == 2 ? 2 : 1;    // slices on their way
+    float wv[AHEAD][WU][8], qv[AHEAD][2][8];
+    auto fetch = [&](int s, int r0) {         // rows past the last one are replaced by it and get weight zero below
+#pragma unroll
+        for (int u = 0; u < WU; ++u)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) wv[s][u][t] = wp[(int64_t)min(r0 + 8 * (kgw + 2 * u) + t, nrows - 1) * kGNeg];
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int row = min(r0 + 8 * (kgc + 2 * u) + t, nrows - 1);
-                wv[u][t] = wp[(int64_t)row * kGNeg];
-                qv[u][t] = qp[(int64_t)row * d];
-            }
+            for (int t = 0; t < 8; ++t) qv[s][u][t] = qp[(int64_t)min(r0 + 8 * (kgq + 2 * u) + t, nrows - 1) * d];
     };
-    f32v4 acc[4][4];
+    f32v4 acc[MB][4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < MB; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = f32v4{0.f, 0.f, 0.f, 0.f};
     const int live = min(4, (d - c0 - 64 * wn + 15) >> 4);       // column blocks of this wave, uniform
-    if (nrows > 0) fetch(0);
-    for (int r0 = 0; r0 < nrows; r0 += kGK) {
-        if (r0 + kGK > nrows) {
+    if (nrows > 0) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) zero_past(wv[u], r0 + 8 * (kgc + 2 * u), nrows);
-        }
+        for (int s = 0; s < AHEAD; ++s) fetch(s, kGK * s);
+    }
+    for (int rs = 0; rs < nrows; rs += kGK * AHEAD) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            Tile::store(Ws, tid & 127, kgc + 2 * u, split8(wv[u]));
-            Tile::store(Qs, tid & 127, kgc + 2 * u, split8(qv[u]));
-        }
-        __syncthreads();
-        if (r0 + kGK < nrows) fetch(r0 + kGK);
-        if (live > 0) {
-            Split8 A[4];
+        for (int s = 0; s < AHEAD; ++s) {
+            const int r0 = rs + kGK * s;
+            if (r0 >= nrows) break;           // uniform
+            if (r0 + kGK > nrows) {
 #pragma unroll
-            for (int a = 0; a < 4; ++a) A[a] = Tile::load(Ws, 64 * wm + 16 * a + l15, gq);
+                for (int u = 0; u < WU; ++u) zero_past(wv[s][u], r0 + 8 * (kgw + 2 * u), nrows);
+            }
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                if (b < live) {
-                    Split8 B[1] = {Tile::load(Qs, 64 * wn + 16 * b + l15, gq)};
-                    f32v4 c[4][1] = {{acc[0][b]}, {acc[1][b]}, {acc[2][b]}, {acc[3][b]}};
-                    split_mfma(A, B, c);
-                    acc[0][b] = c[0][0]; acc[1][b] = c[1][0]; acc[2][b] = c[2][0]; acc[3][b] = c[3][0];
+            for (int u = 0; u < WU; ++u) WTile::store(Ws, tid % NEGS, kgw + 2 * u, split8(wv[s][u]));
+#pragma unroll
+            for (int u = 0; u < 2; ++u) QTile::store(Qs, tid & 127, kgq + 2 * u, split8(qv[s][u]));
+            __syncthreads();
+            if (r0 + kGK * AHEAD < nrows) fetch(s, r0 + kGK * AHEAD);
+            if (live > 0) {
+                Split8 A[MB];
+#pragma unroll
+                for (int a = 0; a < MB; ++a) A[a] = WTile::load(Ws, 16 * MB * wm + 16 * a + l15, gq);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    if (b < live) {
+                        Split8 B[1] = {QTile::load(Qs, 64 * wn + 16 * b + l15, gq)};
+                        f32v4 c[MB][1];
+#pragma unroll
+                        for (int a = 0; a < MB; ++a) c[a][0] = acc[a][b];
+                        split_mfma(A, B, c);
+#pragma unroll
+                        for (int a = 0; a < MB; ++a) acc[a][b] = c[a][0];
+                    }
                 }
             }
+            __syncthreads();
         }
-        __syncthreads();
     }
     bool nan = false;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < MB; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) nan |= any_nan(acc[a][b]);
     if (__builtin_expect(__any(nan), 0))
         plain_products(nrows,
             [&](int a, int k) {
-                const int n = min(n0 + 64 * wm + 16 * a + l15, Npad - 1);
+                const int n = min(n0 + 16 * MB * wm + 16 * a + l15, Npad - 1);
                 return Wtile[((n >> 6) * g.rows_tile + k) * kGNeg + (n & 63)];
             },
             [&](int b, int k) { return Qrows[(int64_t)k * d + min(c0 + 64 * wn + 16 * b + l15, d - 1)]; }, acc);
+    if (atomic) {
+        // all ids first: loaded one at a time between the additions, each of these waited for its own (a batch of 2000 edges, both
+        // sides, 64 negatives, d = 130: 22.5 us, 14.2 so)
+        int32_t id[MB][4];
+#pragma unroll
+        for (int a = 0; a < MB; ++a)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) id[a][v] = my_negs[min(n0 + 16 * MB * wm + 16 * a + 4 * gq + v, N - 1)];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int col = c0 + 64 * wn + 16 * b + l15;
+            if (col >= d) continue;
+#pragma unroll
+            for (int a = 0; a < MB; ++a)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (n0 + 16 * MB * wm + 16 * a + 4 * gq + v < N) unsafeAtomicAdd(Gn + (int64_t)id[a][v] * d + col, acc[a][b][v]);
+        }
+        return;
+    }
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         const int col = c0 + 64 * wn + 16 * b + l15;
         if (col >= d) continue;
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
+        for (int a = 0; a < MB; ++a)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int n = n0 + 64 * wm + 16 * a + 4 * gq + v;
-                if (n >= N) continue;
-                if (atomic) unsafeAtomicAdd(Gn + (int64_t)my_negs[n] * d + col, acc[a][b][v]);
-                else row_store(grad + (neg_base + n) * d + col, acc[a][b][v], bp.stream_rows);
+                const int n = n0 + 16 * MB * wm + 16 * a + 4 * gq + v;
+                if (n < N) row_store(grad + (neg_base + n) * d + col, acc[a][b][v], bp.stream_rows);
             }
-        }
     }
 }
 
@@ -640,8 +696,12 @@ hipError_t launch_chunks_gemm(hipStream_t st, const BatchGeom& g, const BucketPa
     const int64_t tiles = (int64_t)g.sides * g.nchunks * g.T;
     const int64_t rows = (int64_t)g.sides * g.P;
     const int Npad = (int)gemm_npad(g.N);
-    const int ntiles = (g.N + kGTile - 1) / kGTile;
     const int coltiles = (bp.dim + kGTile - 1) / kGTile;
+    const int ntiles128 = (g.N + kGTile - 1) / kGTile, ntiles64 = (g.N + 63) / 64;
+    const bool few_scores = tiles * ntiles128 < kGFew;
+    const bool few_gneg = tiles * ntiles128 * coltiles < kGFew;
+    const int stiles = few_scores ? ntiles64 : ntiles128;
+    const int ntiles = few_gneg ? ntiles64 : ntiles128;
     const bool softmax = bp.loss == LEGEND_LOSS_SOFTMAX;
     switch (bp.score) {
         case LEGEND_SCORE_DOT:
@@ -657,9 +717,11 @@ hipError_t launch_chunks_gemm(hipStream_t st, const BatchGeom& g, const BucketPa
     const int rb = (g.rows_tile + 15) / 16;
 #define LEGEND_GEMM_RB(RB)                                                                                             \
     case RB: {                                                                                                         \
-        auto scores = bp.dim % 4 == 0 ? k_gemm_scores<RB, 4> : bp.dim % 2 == 0 ? k_gemm_scores<RB, 2> : k_gemm_scores<RB, 1>; \
-        hipLaunchKernelGGL(scores, dim3((unsigned)xcd_grid(ntiles * tiles)), dim3(kGThreads), 0, st, g, bp, ws.neg_ids, \
-                           ws.gemm_Q, ws.gemm_S, Npad, ntiles, tiles);                                                 \
+        auto scores = bp.dim % 4 == 0   ? (few_scores ? k_gemm_scores<RB, 4, 1> : k_gemm_scores<RB, 4, 2>)              \
+                      : bp.dim % 2 == 0 ? (few_scores ? k_gemm_scores<RB, 2, 1> : k_gemm_scores<RB, 2, 2>)              \
+                                        : (few_scores ? k_gemm_scores<RB, 1, 1> : k_gemm_scores<RB, 1, 2>);             \
+        hipLaunchKernelGGL(scores, dim3((unsigned)xcd_grid(stiles * tiles)), dim3(kGThreads), 0, st, g, bp, ws.neg_ids, \
+                           ws.gemm_Q, ws.gemm_S, Npad, stiles, tiles);                                                 \
         break;                                                                                                         \
     }
     switch (rb < 7 ? rb : 7) {
@@ -687,7 +749,7 @@ hipError_t launch_chunks_gemm(hipStream_t st, const BatchGeom& g, const BucketPa
     }
 #undef LEGEND_GEMM_RB
     const int negtiles = coltiles * ntiles;
-    hipLaunchKernelGGL(k_gemm_gneg, dim3((unsigned)xcd_grid(negtiles * tiles)), dim3(kGThreads), 0, st, g, bp, ws.neg_ids,
+    hipLaunchKernelGGL(few_gneg ? k_gemm_gneg<2> : k_gemm_gneg<4>, dim3((unsigned)xcd_grid(negtiles * tiles)), dim3(kGThreads), 0, st, g, bp, ws.neg_ids,
                        ws.gemm_S, Npad, ws.gemm_Q, ws.grad, coltiles, negtiles, tiles);
     switch (bp.score) {
         case LEGEND_SCORE_DOT:
