@@ -117,9 +117,9 @@ struct legend_ctx {
     hipEvent_t ev_index[3] = {nullptr, nullptr, nullptr};    // index side of a batch complete (per workspace)
     hipEvent_t ev_updated[3] = {nullptr, nullptr, nullptr};  // update of a batch complete: its index buffers are free
     Workspace ws{};                         // even batches of a call; also every serial path
-    Workspace ws_alt[2]{};                  // batches 1 and 2 (mod 3): own index-side buffers, the rest shared with ws
+    Workspace ws_alt[2]{};                  // batches 1 and 2 (mod 3): own index-side buffers, the rest shared with ws; empty where small_slabs are
     BatchGeom gmax{};
-    uint32_t* small_slabs = nullptr;        // two sets of kSmallGroup slabs where a full batch is small, else null
+    uint32_t* small_slabs = nullptr;        // two sets of kSmallGroup slabs (5.3 MB) where a full batch is small, else null
     int key_bits = 0;
     int32_t* edges_dev = nullptr;
     int64_t edges_cap = 0;
@@ -132,7 +132,7 @@ struct legend_ctx {
     double prof_ms[KC_COUNT] = {0};
     int64_t prof_launches[KC_COUNT] = {0};
     int64_t batches_done = 0;
-    bool index_after_chunk = false;         // LEGEND_INDEX_AFTER_CHUNK=1: the next batch's index side starts when this batch's chunk kernel has finished, not when it is launched (a measurement knob)
+    bool index_after_chunk = false;         // LEGEND_INDEX_AFTER_CHUNK=1: the next batch's index side starts when this batch's chunk kernel has finished, not when it is launched (a measurement knob) (no effect on small batches, whose index sides are made in groups)
     int32_t stream_rows = -1;               // LEGEND_STREAM_ROWS=0 or 1: never or always (tests compare the two); else streams_rows decides
     bool no_small_update = false;           // LEGEND_NO_SMALL_UPDATE=1: small batches take the general update kernels too (tests compare the two)
     bool serial_sort = false;               // LEGEND_SERIAL_SORT=1: everything on the compute stream, batch after batch (for per-kernel timing)
@@ -682,7 +682,7 @@ int legend_init_partitions(const legend_config* cfg, const float* init_node_emb,
     Workspace& w = c->ws;
     w.cap_occ = occ;
     w.cap_wg = nwg;
-    if (occ <= kSmallSortMax) INIT_RC(dev_alloc(c, &c->small_slabs, (size_t)2 * kSmallGroup * SmallSlab::words));
+    if (occ <= kSmallSortMax && !c->serial_sort) INIT_RC(dev_alloc(c, &c->small_slabs, (size_t)2 * kSmallGroup * SmallSlab::words));
     INIT_RC(dev_alloc(c, &w.neg_ids, (size_t)c->gmax.sides * c->gmax.nchunks * c->gmax.N));
     for (int k = 0; k < 2; ++k) {
         INIT_RC(dev_alloc(c, &w.keys[k], (size_t)occ));
@@ -722,8 +722,8 @@ int legend_init_partitions(const legend_config* cfg, const float* init_node_emb,
     }
     // Two more sets of index-side buffers: the index side of batch b+1 is built while batch b is still
     // being computed and applied, into the set that batch b-2 has released (so it does not wait for
-    // the update of batch b-1 either).
-    for (Workspace& o : c->ws_alt) {
+    // the update of batch b-1 either).  Small batches have the slabs instead, serial ones need neither.
+    if (!c->small_slabs && !c->serial_sort) for (Workspace& o : c->ws_alt) {
         o = w;
         o.neg_ids = nullptr; o.keys[0] = o.keys[1] = nullptr; o.vals[0] = o.vals[1] = nullptr;
         o.ghist = nullptr; o.scan_tmp = nullptr; o.uniq_keys = nullptr; o.seg_start = nullptr; o.counters = nullptr;
