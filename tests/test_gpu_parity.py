@@ -81,6 +81,10 @@ _TRANS_EDGES = [
     _case("transe_d68_rows57", TRANSE, LOGISTIC, DST, 1_500, 3, 68, 1, 0, 0, 171, 57, 130, 5, 400, 0.3),
     _case("transe_d97_rows64", TRANSE, SOFTMAX, DST, 1_500, 3, 97, 1, 0, 0, 192, 64, 100, 0, 400, 0.3),
     dict(_case("transe_d36_tiny_components", TRANSE, MARGIN, BOTH, 1_500, 3, 36, 1, 0, 0, 150, 50, 70, 0, 300, 1e-23), margin=1.03),
+    # some rows with components above 2^25 (their tiles compare, the others do not), and weights above 128
+    dict(_case("transe_d36_large_components", TRANSE, LOGISTIC, BOTH, 1_500, 3, 36, 1, 0, 0, 150, 50, 130, 0, 300, 0.02),
+         hot_every=64, hot_scale=5e9),
+    dict(_case("transe_d12_large_weight", TRANSE, LOGISTIC, BOTH, 1_500, 3, 12, 1, 0, 0, 150, 50, 70, 0, 300, 0.02), neg_weight=400.0),
 ]
 
 # The wide path at the edges of its tiles: 128 negatives, 128 columns, slices of 32, row blocks of 16 up to 112.
@@ -130,7 +134,7 @@ def _ocfg(c):
     return OracleConfig(num_nodes=c["V"], num_relations=c["nrel"], dim=c["d"], num_partitions=c["n"],
                         batch_size=c["B"], chunk_size=c["C"], num_negs=c["N"], num_degree_negs=c["ndeg"],
                         score=c["score"], loss=c["loss"], corrupt=c["corrupt"], lr=0.1, eps=1e-10,
-                        neg_weight=-1.0, seed=c["seed"], margin=c.get("margin", 1.0))
+                        neg_weight=c.get("neg_weight", -1.0), seed=c["seed"], margin=c.get("margin", 1.0))
 
 
 def _gpu_ctx(c, node, rel, capacity=None, update_mode=0):
@@ -139,7 +143,7 @@ def _gpu_ctx(c, node, rel, capacity=None, update_mode=0):
                         update_mode=update_mode,
                         num_relations=c["nrel"], score=c["score"], loss=c["loss"], corrupt=c["corrupt"],
                         batch_size=c["B"], chunk_size=c["C"], num_negs=c["N"], num_degree_negs=c["ndeg"],
-                        lr=0.1, eps=1e-10, seed=c["seed"], margin=c.get("margin", 1.0))
+                        lr=0.1, eps=1e-10, seed=c["seed"], margin=c.get("margin", 1.0), neg_weight=c.get("neg_weight", -1.0))
     ctx = L.legend_init_partitions(cfg, node, rel if c["score"] else None)
     return L, ctx
 

@@ -7,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _run(monkeypatch, serial, calls, m, update_mode=0):
+def _run(monkeypatch, serial, calls, m, update_mode=0, no_small_update=False):
     from paper_2505_09258_amd import binding as L
     V, d, B = 900, 20, 60
     rng = np.random.default_rng(3)
@@ -15,8 +15,9 @@ def _run(monkeypatch, serial, calls, m, update_mode=0):
     rel = (0.3 * rng.standard_normal((4, d))).astype(np.float32)
     edges = np.stack([(V // 2 * rng.random(m) ** 3), rng.integers(0, 4, m), V // 2 * rng.random(m)], 1).astype(np.int32)
     monkeypatch.setenv("LEGEND_SERIAL_SORT", "1" if serial else "0")
+    monkeypatch.setenv("LEGEND_NO_SMALL_UPDATE", "1" if no_small_update else "0")
     cfg = L.make_config(num_nodes=V, dim=d, num_partitions=2, num_relations=4, score=L.SCORE_DISTMULT, corrupt=L.CORRUPT_BOTH,
-                        batch_size=B, chunk_size=20, num_negs=33, num_degree_negs=5, seed=2)
+                        batch_size=B, chunk_size=20, num_negs=33, num_degree_negs=5, seed=2, update_mode=update_mode)
     ctx = L.legend_init_partitions(cfg, node, rel)
     try:
         for p in range(2):
@@ -41,3 +42,30 @@ def test_groups_give_the_bits_of_single_batches(monkeypatch, m, calls):
     assert a == b
     for x, y in zip(ta, tb):
         assert (x == y).all()
+
+
+@pytest.mark.parametrize("m,calls", [(33 * 60 - 59, [(0, 33)] * 2), (80 * 60 - 11, [(3, 40), (10, 80)])])
+def test_groups_with_the_general_update_kernels(monkeypatch, m, calls):
+    """The update kernels of larger batches read their lists from a slab: the same bits again."""
+    a, ta = _run(monkeypatch, False, calls, m, no_small_update=True)
+    b, tb = _run(monkeypatch, True, calls, m)
+    assert a == b
+    for x, y in zip(ta, tb):
+        assert (x == y).all()
+
+
+@pytest.mark.parametrize("m,calls", [(59, [(0, 1)]), (65 * 60 - 7, [(0, 65)])])
+def test_groups_in_atomic_mode(monkeypatch, m, calls):
+    """The atomic update reads its rows from a slab.  Sums in arrival order: the first batch of a run to a few roundings
+    of a gradient (Adagrad's first step is lr times its sign), rows touched and their number exactly."""
+    a, ta = _run(monkeypatch, False, calls, m, update_mode=1)
+    b, tb = _run(monkeypatch, True, calls, m, update_mode=1)
+    assert a[-1] == b[-1]                                      # unique rows of every batch, batches
+    for x, y in zip(a[:-1], b[:-1]):
+        assert abs(x - y) <= 1e-5 * abs(y)
+    for t in (1, 3):                                           # states: zero exactly where nothing was touched
+        assert ((ta[t] != 0) == (tb[t] != 0)).all()
+    if calls == [(0, 1)]:
+        scale = np.sqrt(tb[1].max())                           # the largest gradient element
+        # at most 60 + 3 * 33 terms meet in an element, each off by half a unit of the running sum
+        assert np.abs(np.sqrt(ta[1]) - np.sqrt(tb[1])).max() <= 160 * 2.0 ** -24 * scale
