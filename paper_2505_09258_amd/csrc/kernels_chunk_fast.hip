@@ -181,7 +181,7 @@ struct RowItem {
     }
 };
 
-template <int SCORE, int D>
+template <int SCORE, int D, bool STREAM>      // STREAM: bp.stream_rows (a choice at the store cost 0.6 % of a batch)
 __global__ void __launch_bounds__(kFThreads, 1)
 k_chunk_fast(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, float* __restrict__ grad,
              double* __restrict__ loss_partial, uint32_t* __restrict__ redo, unsigned long long* __restrict__ redo_total,
@@ -733,7 +733,7 @@ k_chunk_fast(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, 
                 const int k = idx / (d / 4);
                 const int n = neg_of(t, 16 * wl + k);
                 if (k < 16 && n < N)
-                    row_store4(grad + (neg_base + n) * d + 4 * (idx - k * (d / 4)), lds4(St + 4 * idx), bp.stream_rows);
+                    row_store4(grad + (neg_base + n) * d + 4 * (idx - k * (d / 4)), lds4(St + 4 * idx), STREAM);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -817,26 +817,26 @@ k_chunk_fast(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, 
 // expensive to compile); every other shape takes the general kernel.  Each score function is
 // compiled in a translation unit of its own (this file with LEGEND_FAST_SCORE set), so that the
 // three compile side by side.
-template <int SC, int D>
+template <int SC, int D, bool STREAM>
 static hipError_t launch_fast_one(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {
     dim3 grid((unsigned)(g.sides * g.nchunks * g.T)), block(kFThreads);
     constexpr size_t lds = FastShape<D>::lds_bytes;
     static PerDeviceFlag configured;
     if (configured.pending()) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chunk_fast<SC, D>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chunk_fast<SC, D, STREAM>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         configured.set();
     }
-    hipLaunchKernelGGL((k_chunk_fast<SC, D>), grid, block, lds, st, g, bp, ws.neg_ids, ws.grad,
+    hipLaunchKernelGGL((k_chunk_fast<SC, D, STREAM>), grid, block, lds, st, g, bp, ws.neg_ids, ws.grad,
                        ws.loss_partial, ws.redo, ws.redo_total, ws.fast_limit, ws.fast_no_rescale ? 0 : 1);
     return hipGetLastError();
 }
 
 template <int SC>
 static hipError_t launch_fast_score(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {
-    if (bp.dim == 100) return launch_fast_one<SC, 100>(st, g, bp, ws);
-    if (bp.dim == 64) return launch_fast_one<SC, 64>(st, g, bp, ws);
+    if (bp.dim == 100) return (bp.stream_rows ? launch_fast_one<SC, 100, true> : launch_fast_one<SC, 100, false>)(st, g, bp, ws);
+    if (bp.dim == 64) return (bp.stream_rows ? launch_fast_one<SC, 64, true> : launch_fast_one<SC, 64, false>)(st, g, bp, ws);
     return hipErrorInvalidValue;
 }
 
