@@ -301,44 +301,38 @@ k_long_partial(const uint32_t* __restrict__ counters, const uint32_t* __restrict
     }
 }
 
-// One group per long row: its units' partial rows are added in unit order, then Adagrad.  Eight units' loads go out
-// together: a single relation's row of 50 000 gradient rows has 196 of them (one after the other 172 us a batch; the bucket of
-// six such batches 14.2 -> 13.7 ms).  Letting rows of up to 128 gradient rows in large batches go without units was no
-// gain (d = 400: 36.5 -> 37.7 ms an epoch).
-template <int LPR>
-__global__ void __launch_bounds__(256)
+// One thread per element of a long row: its units' partial sums are added in unit order, then Adagrad.  Eight units' loads go out
+// together: a single relation's row of 50 000 gradient rows has 196 of them (one after the other 172 us a batch).  The kernel
+// runs beside k_update on a stream of its own and has to fit next to its waves: with four columns a thread the eight loads took 121
+// registers, and the launch waited for compute units to run empty (1M nodes, 50 000 edges: 30 us with 60 registers, 253 us
+// with 121, into the next batch's chunk kernel).  Letting rows of up to 128 gradient rows in large batches go without units
+// was no gain (d = 400: 36.5 -> 37.7 ms an epoch).
+__global__ void __launch_bounds__(256, 8)
 k_long_final(const uint32_t* __restrict__ counters, const uint32_t* __restrict__ long_list,
              const uint32_t* __restrict__ unit_start, const uint32_t* __restrict__ uniq_keys,
              const double* __restrict__ partial, UpdateTables tb, int d, float lr, float eps) {
-    const int groups_per_block = 256 / LPR;
-    const int gl = threadIdx.x / LPR;
-    const int col4 = threadIdx.x % LPR;
-    const int c0 = col4 * 4;
-    const bool vec4 = (d & 3) == 0;
-    const uint32_t n_long = counters[2];
-    for (uint32_t r = blockIdx.x * groups_per_block + gl; r < n_long; r += gridDim.x * groups_per_block) {
-        for (int cc = c0; cc < d; cc += 4 * LPR) {
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            const uint32_t last = unit_start[r + 1];
-            const int cols = min(4, d - cc);
-            uint32_t unit = unit_start[r];
-            for (; unit + 8 <= last; unit += 8) {
-                double v[8][4];
+    const uint32_t n = counters[2] * (uint32_t)d;         // a batch has fewer than 2^17 long rows (sort limit), d <= 512
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+        const uint32_t r = i / (uint32_t)d, c = i - r * (uint32_t)d;
+        const uint32_t last = unit_start[r + 1];
+        uint32_t unit = unit_start[r];
+        const double* p = partial + (int64_t)unit * d + c;
+        double acc = 0.0;
+        for (; unit + 8 <= last; unit += 8, p += (int64_t)8 * d) {
+            double v[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
+            for (int k = 0; k < 8; ++k) v[k] = p[(int64_t)k * d];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) v[k][j] = partial[(int64_t)(unit + k) * d + cc + min(j, cols - 1)];
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[j] += v[k][j];
-            }
-            for (; unit < last; ++unit) {     // most long rows have one unit
-                const double* pp = partial + (int64_t)unit * d + cc;
-                for (int j = 0; j < cols; ++j) acc[j] += pp[j];
-            }
-            apply_row(tb, uniq_keys[long_list[r]], acc, d, cc, vec4, lr, eps);
+            for (int k = 0; k < 8; ++k) acc += v[k];
         }
+        for (; unit < last; ++unit, p += d) acc += *p;    // most long rows have one unit
+        const uint32_t key = uniq_keys[long_list[r]];
+        const int t = table_of_key(tb, key);
+        const int64_t at = (int64_t)(key - tb.key_base[t]) * d + c;
+        float th = tb.E[t][at], st = tb.S[t][at];
+        adagrad_elem((float)acc, th, st, lr, eps);
+        tb.E[t][at] = th;
+        tb.S[t][at] = st;
     }
 }
 
@@ -409,9 +403,10 @@ static hipError_t launch_update_lpr(hipStream_t st, const BatchGeom& g, const Bu
     int64_t ublocks = max_units < 2048 ? max_units : 2048;
     hipLaunchKernelGGL((k_long_partial<LPR, STREAM>), dim3((unsigned)ublocks), dim3(256), sizeof(double) * 4 * 256, st, ws.counters,
                        ws.long_list, ws.unit_start, ws.seg_start, sorted_vals, ws.grad, d, ws.long_partial);
-    int64_t fblocks = (g.n_occ / (kLongLen + 1) + groups) / groups;
+    int64_t fblocks = (g.n_occ / (kLongLen + 1) * d + 255) / 256;
     if (fblocks > 1024) fblocks = 1024;
-    hipLaunchKernelGGL(k_long_final<LPR>, dim3((unsigned)fblocks), dim3(256), 0, st, ws.counters, ws.long_list,
+    if (fblocks < 1) fblocks = 1;
+    hipLaunchKernelGGL(k_long_final, dim3((unsigned)fblocks), dim3(256), 0, st, ws.counters, ws.long_list,
                        ws.unit_start, ws.uniq_keys, ws.long_partial, tb, d, bp.lr, bp.eps);
     return hipGetLastError();
 }
