@@ -15,10 +15,10 @@
 // contraction elements with 128 (small batches: 64) columns or negatives to a tile, the next slice on its way from memory; about 50 KB of
 // LDS and at most 168 registers leave three workgroups to a compute unit, which cut and multiply in turn.  An operand whose contraction
 // index is the slow one in memory is loaded by one thread per column, eight rows each: whole lines per instruction.
-// Measured on batches of 10 000 edges, both sides, 1000 negatives, d = 400 (200 row tiles of 100): G_Q 276 -> 161 us, G_neg 255 ->
-// 178 us, an epoch of 49 batches with its read 52.0 -> 39.4 ms.  What bounds them now: vector instructions of the cutting
+// Measured on batches of 10 000 edges, both sides, 1000 negatives, d = 400 (200 row tiles of 100): G_Q 276 -> 166 us, G_neg 255 ->
+// 167 us, an epoch of 49 batches with its read 51.9 -> 36.4 ms.  What bounds them now: vector instructions of the cutting
 // and matrix instructions take about a fifth of the time each, the rest waits for slices gathered from the tables.  Below
-// d = 128 the chain loses to the two-sweep kernel (d = 50, 50 000 edges a batch: 14.1 against 12.7 ms an epoch), also with
+// d = 128 the chain loses to the two-sweep kernel (d = 50, 50 000 edges a batch: 14.1 against 13.9 ms an epoch), with
 // the scores taken in turns that stay in the Infinity cache.
 #include "chunk_common.h"
 #include "split_bf16.h"
