@@ -132,7 +132,7 @@ struct legend_ctx {
     double prof_ms[KC_COUNT] = {0};
     int64_t prof_launches[KC_COUNT] = {0};
     int64_t batches_done = 0;
-    bool index_after_chunk = false;         // LEGEND_INDEX_AFTER_CHUNK=1: the next batch's index side starts when this batch's chunk kernel has finished, not when it is launched (a measurement knob) (no effect on small batches, whose index sides are made in groups)
+    bool index_after_chunk = false;         // LEGEND_INDEX_AFTER_CHUNK=1: the next batch's index side starts when this batch's chunk kernel has finished, not when it is launched (a measurement knob; no effect on small batches, whose index sides are made in groups)
     int32_t stream_rows = -1;               // LEGEND_STREAM_ROWS=0 or 1: never or always (tests compare the two); else streams_rows decides
     bool no_small_update = false;           // LEGEND_NO_SMALL_UPDATE=1: small batches take the general update kernels too (tests compare the two)
     bool serial_sort = false;               // LEGEND_SERIAL_SORT=1: everything on the compute stream, batch after batch (for per-kernel timing)
