@@ -25,7 +25,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 MFMA_F32_PEAK_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
-# fp32 products as six bf16 part products (dimensions above 128, ranking): a sixth of the dense bf16 matrix peak
+# fp32 products as six bf16 part products (training but for small or atomic batches up to 128 dimensions, ranking): a sixth of the dense bf16 matrix peak
 MFMA_SPLIT_PEAK_TFLOPS = 2500.0 / 6
 # fp32 vector peak of the instructions this build issues (packed fp32 is switched off): 256 CUs x 64 lanes x 2.4 GHz
 # = 39.3 T instructions/s; a fused multiply-add counts two operations (78.6 TFLOP/s), anything else one (39.3 T op/s)
@@ -376,18 +376,19 @@ def run_resident(args, w, K, W, L, graphs, torch, np, *, kernels_pass=True, cpu_
     Q = sides * (-(-P // w.chunk_size)) * N
     u_b = uniq / max(nbatches, 1)
     alg_bytes = 12 * P + 4 * Q + 4 * d * (2 * P + Q) + 16 * d * u_b
-    single_sweep = (w.dim in (100, 64) and w.loss == graphs.LOSS_SOFTMAX and w.num_negs <= 1024 and args.update_mode != "atomic"
-                    and w.score != graphs.SCORE_TRANSE_L1 and os.environ.get("LEGEND_NO_FAST_CHUNK") != "1")
+    small = shape["occurrences"] <= 4096
+    split = w.dim > 128 or (args.update_mode != "atomic" and os.environ.get("LEGEND_NO_FAST_CHUNK") != "1" and
+                            (N * d >= 5000 or (N * d >= 2500 and d > 32 and (w.loss == graphs.LOSS_SOFTMAX or small))))
     kname = ("k_gemm_compose/scores/rowstats/gq/gneg/chain (one launch each)" if w.dim > 128
-             else ("k_chunk_fast" if single_sweep else "k_chunk"))
-    traffic = TRAFFIC_BYTES.get(w.name.split("+")[0], {})
-    mfma_peak = MFMA_SPLIT_PEAK_TFLOPS if w.dim > 128 else MFMA_F32_PEAK_TFLOPS
-    how = "fp32 as six bf16 MFMA products" if w.dim > 128 else "fp32 MFMA"
+             else ("k_chunk_split" if split else "k_chunk"))
+    traffic = TRAFFIC_BYTES.get(w.name.split("+")[0], {}) if kname == "k_chunk_split" else {}
+    mfma_peak = MFMA_SPLIT_PEAK_TFLOPS if split else MFMA_F32_PEAK_TFLOPS
+    how = "fp32 as six bf16 MFMA products" if split else "fp32 MFMA"
     roofline = {"kernel": f"{kname} (gather + scores + loss + backward, {how})", "bound": "mfma",
                 "achieved": round(achieved_tflops, 3), "peak": round(mfma_peak, 1), "unit": "TFLOP/s",
                 "frac": round(achieved_tflops / mfma_peak, 4),
-                "traffic": traffic.get("chunk") if single_sweep else None,
-                "traffic_source": traffic.get("source") if single_sweep else None,
+                "traffic": traffic.get("chunk"),
+                "traffic_source": traffic.get("source"),
                 "flops_per_launch": flops_per_launch, "avg_launch_ms": round(chunk_ms, 4)}
     translational = w.score == graphs.SCORE_TRANSE_L1
     if translational:
@@ -607,7 +608,7 @@ def main() -> int:
         "hbm_GBs_whole_step": round(res["alg_bytes"] / (res["ms_per_step"] * 1e-3) / 1e9, 1),
         "copy_GBs_measured": round(res["copy_gbs"], 1) if res["copy_gbs"] else None,
         "roofline": res["roofline"], "update": res["update"], "kernels": res["kernels"],
-        # workgroups (of K x 1000 x sides) whose single-sweep softmax reference was raised on the way: a tuning aid
+        # workgroups (of K x 1000 x sides) whose softmax reference was raised on the way: a tuning aid
         "raised_reference_workgroups": res["fallback_chunks"],
         "update_mode_note": "deterministic is the fast mode: the atomic mode measures 2.1e7 edges/s on c2 against 5.0e7 "
                             "(1.1e8 fp32 atomics per batch cost 1.3 ms, profiles/c2_atomic_kernel_trace.txt)",

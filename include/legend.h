@@ -306,11 +306,11 @@ int legend_batch_shape_of(legend_ctx* ctx, legend_batch_shape* out);
 /* Unique rows updated by the batches since the last call (sum), then cleared. */
 int legend_unique_rows_read(legend_ctx* ctx, int64_t* unique_rows, int64_t* batches);
 
-/* Workgroups (one row tile of one chunk) of the single-sweep batch kernel that met
- * a score too far above their softmax reference (the reference is then raised in
- * place and what was accumulated rescaled, or the chunk handed over to the
- * two-sweep kernel) since the last call, then cleared.  A tuning aid: 0 early in
- * training. */
+/* Workgroups (one row tile of one chunk) of the batch kernel on bf16 parts (product scores,
+ * dim <= 128, softmax losses) that met a score too far above their softmax reference (the
+ * reference is then raised on the way) or a number that is not finite (the chunk is then
+ * handed over to the fp32 kernel) since the last call, then cleared.  A tuning aid: 0 early
+ * in training. */
 int legend_fallback_chunks_read(legend_ctx* ctx, int64_t* chunks);
 
 /*

@@ -18,8 +18,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "liblegend_hip.so")
 
-SOURCES = ["runtime.hip", "kernels_prepare.hip", "kernels_sort.hip", "kernels_chunk.hip", "kernels_chunk_gemm.hip", "kernels_chunk_fast.hip", "kernels_chunk_fast_distmult.hip", "kernels_chunk_fast_complex.hip",
+SOURCES = ["runtime.hip", "kernels_prepare.hip", "kernels_sort.hip", "kernels_chunk.hip", "kernels_chunk_gemm.hip", "kernels_chunk_split.hip",
            "kernels_update.hip", "kernels_rank.hip", "kernels_chunk_trans.hip", "order_plan.cpp"]
+# translation units of one source with one value of a macro each: source, macro, values
+VARIANTS = [("kernels_chunk_split.hip", "LEGEND_SPLIT_NJ", (2, 4, 6, 7, 8))]
 
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -43,10 +45,11 @@ def build_library(verbose: bool = False) -> str:
     os.makedirs(obj_dir, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
-    def compile_one(src: str) -> str:
-        obj = os.path.join(obj_dir, os.path.splitext(src)[0] + ".o")
+    def compile_one(unit) -> str:
+        src, suffix, defines = unit
+        obj = os.path.join(obj_dir, os.path.splitext(src)[0] + suffix + ".o")
         lang = ["-x", "hip"] if src.endswith(".cpp") else []
-        cmd = [hipcc, *HIP_FLAGS, *inc, "-c", *lang, os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *HIP_FLAGS, *defines, *inc, "-c", *lang, os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
@@ -54,8 +57,10 @@ def build_library(verbose: bool = False) -> str:
             print(r.stderr, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        objs = list(ex.map(compile_one, SOURCES))
+    units = [(src, f"_{v}", [f"-D{macro}={v}"]) for src, macro, values in VARIANTS for v in values]
+    units += [(src, "", []) for src in SOURCES]
+    with ThreadPoolExecutor(max_workers=min(8, len(units))) as ex:
+        objs = list(ex.map(compile_one, units))
     tmp = LIB_PATH + ".tmp"
     r = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp],
                        capture_output=True, text=True)

@@ -40,7 +40,7 @@ template <int NB, int SCORE, int LOSS, int DFIX>
 __global__ void __launch_bounds__(kChunkThreads, 2)     // two waves per SIMD: two workgroups share a compute unit
 k_chunk(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids, float* __restrict__ grad,
         double* __restrict__ loss_partial, const uint32_t* __restrict__ only_if) {
-    // redo mode: only the workgroups the single-sweep kernel flagged have anything to do
+    // redo mode: only the workgroups the kernel on bf16 parts flagged have anything to do
     if (only_if && only_if[blockIdx.x] == 0u) return;
     constexpr int LPR = NB * 8;             // lanes that cooperate on one gathered row (float4 each)
     constexpr int RPS = kWave / LPR;        // rows a wave gathers per step
@@ -641,17 +641,17 @@ static hipError_t launch_chunks_nb(hipStream_t st, const BatchGeom& g, const Buc
     return hipErrorInvalidValue;
 }
 
-bool chunks_use_single_sweep(const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {
-    return g.P > 0 && bp.score != LEGEND_SCORE_TRANSE_L1 && chunk_fast_applies(g, bp) && !ws.no_fast_path;
+bool chunks_use_split(const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {
+    return g.P > 0 && chunk_split_applies(g, bp) && !ws.no_fast_path;
 }
 
-// redo = false: the batch computation proper.  redo = true (only after a single-sweep launch):
-// the two-sweep kernel over the workgroups the single-sweep kernel flagged as out of range.
+// redo = false: the batch computation proper.  redo = true (only after a launch of the
+// kernel on bf16 parts): the fp32 kernel over the workgroups that one flagged.
 hipError_t launch_chunks(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws, bool redo) {
     if (g.P <= 0) return hipSuccess;
-    const bool single = chunks_use_single_sweep(g, bp, ws);
-    if (redo && !single) return hipSuccess;
-    if (!redo && single) return launch_chunks_fast(st, g, bp, ws);
+    const bool split = chunks_use_split(g, bp, ws);
+    if (redo && !split) return hipSuccess;
+    if (!redo && split) return launch_chunks_split(st, g, bp, ws);
     if (bp.score == LEGEND_SCORE_TRANSE_L1) return launch_chunks_trans(st, g, bp, ws);
     const uint32_t* only_if = redo ? ws.redo : nullptr;
     // the dimensions of the paper's workloads get kernels with the dimension folded in

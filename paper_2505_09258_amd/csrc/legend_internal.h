@@ -21,7 +21,7 @@ enum KernelClass : int {
     KC_SORT,          // radix sort passes (histogram, scan, scatter) + segment heads
     KC_CHUNK,         // fused gather + scores + loss + backward per chunk (MFMA)
     KC_UPDATE,        // segmented gradient reduce + Adagrad (table rows with few gradient rows)
-    KC_CHUNK_REDO,    // two-sweep kernel over the chunks the single-sweep kernel handed back
+    KC_CHUNK_REDO,    // fp32 kernel over the chunks the kernel on bf16 parts handed back
     KC_MISC,          // loss reduction, validation, scoring
     KC_UPDATE_LONG,   // the same for table rows with many gradient rows (two-level sums), on a stream of its own
     KC_COUNT
@@ -108,7 +108,7 @@ struct Workspace {
     unsigned long long* uniq_total;  // running sum of unique rows
     float*    grad;           // [n_occ][dim] staged gradient rows
     double*   loss_partial;   // one per chunk workgroup
-    uint32_t* redo;           // per chunk workgroup: 1 = the single-sweep kernel left it to the general kernel
+    uint32_t* redo;           // per chunk workgroup: 1 = the kernel on bf16 parts left it to the fp32 kernel
     unsigned long long* redo_total;  // running count of such workgroups
     // dim > 128 only: operands and intermediate results of the chain of contractions
     float*    gemm_Q;         // [sides][P][dim] composed rows
@@ -116,9 +116,9 @@ struct Workspace {
     float*    gemm_S;         // [row tiles][rows_tile][N rounded up to 64] negative scores, then the weights dL/dS
     float*    gemm_a;         // [sides][P] dL/df
     float*    gemm_G;         // [sides][P][dim] G_Q
-    int32_t   no_fast_path;   // LEGEND_NO_FAST_CHUNK=1: always use the general two-sweep kernel
-    int32_t   fast_no_rescale;  // LEGEND_FAST_CHUNK_NO_RESCALE=1: a chunk that would raise its softmax reference goes to the two-sweep kernel instead
-    float     fast_limit;     // how far above its row's current reference a score may lie before the single-sweep kernel raises the reference (LEGEND_FAST_CHUNK_LIMIT, default 110)
+    int32_t   no_fast_path;   // LEGEND_NO_FAST_CHUNK=1: always use the fp32 kernel
+    int32_t   fast_no_rescale;  // LEGEND_FAST_CHUNK_NO_RESCALE=1: a chunk that would raise its softmax reference goes to the fp32 kernel instead
+    float     fast_limit;     // how far above its row's current reference a score may lie before the kernel raises the reference (LEGEND_FAST_CHUNK_LIMIT, default 110)
     double*   loss_sum;       // running bucket loss
     int64_t   cap_occ;
     int64_t   cap_wg;
@@ -157,8 +157,8 @@ hipError_t launch_sort_and_segments(hipStream_t st, const BatchGeom& g, const Bu
                                     const Workspace& ws, int* out_buf, bool plan_long);
 // long rows and their units from the segment bounds; nothing to do for n_occ <= kSmallSortMax
 hipError_t launch_long_plan(hipStream_t st, int64_t n_occ, const Workspace& ws);
-// redo = false: the batch computation; redo = true: second launch over the workgroups the single-sweep kernel flagged
-bool chunks_use_single_sweep(const BatchGeom& g, const BucketParams& bp, const Workspace& ws);
+// redo = false: the batch computation; redo = true: second launch over the workgroups the kernel on bf16 parts flagged
+bool chunks_use_split(const BatchGeom& g, const BucketParams& bp, const Workspace& ws);
 hipError_t launch_chunks(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws, bool redo);
 hipError_t launch_update(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws,
                          const uint32_t* sorted_vals, bool long_rows);

@@ -928,7 +928,7 @@ int legend_train_bucket_range(legend_ctx* c, int32_t i, int32_t j, const int32_t
             ProfScope ps(c, KC_CHUNK);
             HIP_TRY(c, launch_chunks(c->compute, g, bp, ws, false));
         }
-        if (chunks_use_single_sweep(g, bp, ws)) {
+        if (chunks_use_split(g, bp, ws)) {
             ProfScope ps(c, KC_CHUNK_REDO);
             HIP_TRY(c, launch_chunks(c->compute, g, bp, ws, true));
         }
