@@ -22,7 +22,7 @@
 //
 // Tried: the operand of the scores loaded by neighbouring lanes and exchanged between lanes in registers (216 more vector instructions a
 // tile, no faster); the gradient rows staged in LDS with three barriers a step (0.48 ms, but d = 50 0.67); the consumers bringing the
-// negatives into LDS (they become the slower half); loads of the first tile ahead of the positives' rows (no difference).
+// negatives into LDS (they become the slower half); loads of the first tile ahead of the positives' rows (they are waited for first: slower).
 #include <type_traits>
 
 #include "chunk_common.h"
@@ -74,7 +74,7 @@ __device__ __forceinline__ void split_mfma_low(const Split8 (&A)[RA], const Spli
 }
 
 // Both LDS layouts are made of 8-byte chunks, four bf16 of one part: the composed rows as [part][chunk of 4 columns][64 rows], a
-// weight tile as [part][chunk of 4 rows][32 negatives].  A lane reads two chunks of its row for an operand whose contraction index
+// weight tile as [part][chunk of 4 rows][64 negatives].  A lane reads two chunks of its row for an operand whose contraction index
 // is the chunked one, and the transposing read (16 lanes: 4 rows x 4 chunks) serves the other direction.  The row index is
 // crossed with the chunk number so that both kinds of read, and the stores, touch every bank once: chunk bit 0 flips row
 // bits 2 and 4, chunk bit 1 row bit 3.
@@ -96,15 +96,6 @@ __device__ __forceinline__ float row16(float x, F&& f) {
 __device__ __forceinline__ float row16_sum(float x) { return row16(x, [](float a, float b) { return a + b; }); }
 __device__ __forceinline__ float row16_max(float x) { return row16(x, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ uint4 join(uint2 a, uint2 b) { return make_uint4(a.x, a.y, b.x, b.y); }
-
-// compile-time loop: the body gets its index as an integral constant, so that arrays indexed by it stay in registers
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
 
 template <int NJ>
 struct SplitShape {
@@ -187,83 +178,13 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     // endpoints and relations of the wave's eight rows w, w + 8, ...: lanes 3 u .. 3 u + 2 hold those of the u-th
     constexpr int RPW = kSRow / kSWaves;
     const int eids = lane < 3 * RPW && w + kSWaves * (lane / 3) < nrows ? eb[(w + kSWaves * (lane / 3)) * 3 + lane % 3] : 0;
+    const int T64 = (N + 63) >> 6;
+    const int ntiles = 2 * T64;
     for (int k = tid; k < min(N, kIdsLds); k += kSThreads) ids_s[k] = my_negs[k];
     if (tid < 16) flag_s[tid] = 0;
 
-    // ---- composed rows: a wave takes rows w, w + 8, ..., its lanes the columns ------------------------------------------
-    auto put = [&](int row, int k, float v) __attribute__((always_inline)) {
-        const int ch = k >> 2;
-        char* p = Qt + ch * (kSRow * 8) + ((row ^ chunk_cross(ch)) * 8) + (k & 3) * 2;
-        uint32_t hh, mm, ll;
-        split_pair(v, 0.f, hh, mm, ll);
-        *reinterpret_cast<uint16_t*>(p) = (uint16_t)hh;
-        *reinterpret_cast<uint16_t*>(p + PB) = (uint16_t)mm;
-        *reinterpret_cast<uint16_t*>(p + 2 * PB) = (uint16_t)ll;
-    };
-    // x, y, r at the lane's two columns (ComplEx: the two halves of its component) of the wave's eight rows w, w + 8, ...; all
-    // loads of them go out together
-    const bool cplx = bp.score == LEGEND_SCORE_COMPLEX, uses_rel = bp.score != LEGEND_SCORE_DOT;
-    const int k0 = lane, k1 = cplx ? lane + h : lane + 64;
-    const bool ok0 = cplx ? lane < h : lane < d;
-    const bool ok1 = cplx ? lane < h : lane + 64 < d;
-    const bool two = cplx || d > 64;          // uniform: the second column exists
-    struct RowVals { float x0, x1, y0, y1, r0, r1; };
-    auto load_rows = [&](int ids, RowVals (&v)[RPW]) __attribute__((always_inline)) {
-        const int c0 = ok0 ? k0 : 0, c1 = ok1 ? k1 : 0;
-#pragma unroll
-        for (int u = 0; u < RPW; ++u) {
-            const float* x = Ex + (int64_t)__builtin_amdgcn_readlane(ids, 3 * u + xcol) * d;
-            const float* y = Ey + (int64_t)__builtin_amdgcn_readlane(ids, 3 * u + ycol) * d;
-            v[u] = RowVals{x[c0], 0.f, y[c0], 0.f, 1.f, 1.f};
-            if (two) { v[u].x1 = x[c1]; v[u].y1 = y[c1]; }
-            if (uses_rel) {
-                const float* r = bp.E_rel + (int64_t)__builtin_amdgcn_readlane(ids, 3 * u + 1) * d;
-                v[u].r0 = r[c0];
-                if (two) v[u].r1 = r[c1];
-            }
-        }
-    };
-    auto compose = [&](const RowVals& v, float& q0, float& q1) __attribute__((always_inline)) {
-        if (bp.score == LEGEND_SCORE_DOT) { q0 = v.x0; q1 = v.x1; }
-        else if (bp.score == LEGEND_SCORE_DISTMULT) { q0 = v.x0 * v.r0; q1 = v.x1 * v.r1; }
-        else if (side == 0) { q0 = v.x0 * v.r0 - v.x1 * v.r1; q1 = v.x0 * v.r1 + v.x1 * v.r0; }
-        else                { q0 = v.r0 * v.x0 + v.r1 * v.x1; q1 = v.r0 * v.x1 - v.r1 * v.x0; }
-    };
-    {
-        RowVals v[RPW];
-        load_rows(eids, v);
-        float f[RPW];
-#pragma unroll
-        for (int u = 0; u < RPW; ++u) {
-            const int row = w + kSWaves * u;
-            float q0, q1;
-            compose(v[u], q0, q1);
-            if (!ok0 || row >= nrows) q0 = 0.f;
-            if (!ok1 || row >= nrows) q1 = 0.f;
-            f[u] = (ok0 && row < nrows ? q0 * v[u].y0 : 0.f) + (ok1 && row < nrows ? q1 * v[u].y1 : 0.f);
-            if (cplx) {
-                if (ok0) { put(row, k0, q0); put(row, k1, q1); }
-                if (d + lane < 16 * NJ) put(row, d + lane, 0.f);
-            } else {
-                if (k0 < 16 * NJ) put(row, k0, q0);
-                if (k1 < 16 * NJ) put(row, k1, q1);
-            }
-        }
-#pragma unroll
-        for (int m = 32; m > 0; m >>= 1)
-#pragma unroll
-            for (int u = 0; u < RPW; ++u) f[u] += wave_shfl_xor(f[u], m);
-        if (lane == 0) {
-#pragma unroll
-            for (int u = 0; u < RPW; ++u) f_s[w + kSWaves * u] = f[u];
-        }
-    }
-    __syncthreads();
-
     // ---- negatives: column k of 64-tile t is negative k T + t (every tile is an even sample of the chunk's negatives, so that
     // the first tile's row maxima are a good softmax reference); a wave's tile i is one half of 64-tile i / 2 -----------------
-    const int T64 = (N + 63) >> 6;
-    const int ntiles = 2 * T64;
     auto neg_at = [&](int i, int k) __attribute__((always_inline)) { return (32 * (i & 1) + k) * T64 + (i >> 1); };
     auto live = [&](int i) __attribute__((always_inline)) { return i < ntiles && neg_at(i, 0) < N; };
     const bool ids_in_lds = N <= kIdsLds;
@@ -327,13 +248,89 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb) rows[nb] = En + (int64_t)id_of(neg_at(i, 16 * (nb ^ swap) + l15)) * d;
     };
-    auto gather = [&](int i) __attribute__((always_inline)) {
-        const float* rows[2];
-        rows_of(i, 0, rows);
+    // The first tile's loads go out behind those of the positives' rows and are not waited for with them (loads return in order).
+    // Its ids are not in LDS yet.
+    const int first = !SOFT || !live(w) ? (w & 3) >> 1 : w;
+    int first_id[2];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) raw_load(rows, ks);
-        raw_load_tail(rows);
+    for (int nb = 0; nb < 2; ++nb) first_id[nb] = my_negs[min(neg_at(first, 16 * nb + l15), N - 1)];
+
+    // ---- composed rows: a wave takes rows w, w + 8, ..., its lanes the columns ------------------------------------------
+    auto put = [&](int row, int k, float v) __attribute__((always_inline)) {
+        const int ch = k >> 2;
+        char* p = Qt + ch * (kSRow * 8) + ((row ^ chunk_cross(ch)) * 8) + (k & 3) * 2;
+        uint32_t hh, mm, ll;
+        split_pair(v, 0.f, hh, mm, ll);
+        *reinterpret_cast<uint16_t*>(p) = (uint16_t)hh;
+        *reinterpret_cast<uint16_t*>(p + PB) = (uint16_t)mm;
+        *reinterpret_cast<uint16_t*>(p + 2 * PB) = (uint16_t)ll;
     };
+    // x, y, r at the lane's two columns (ComplEx: the two halves of its component) of the wave's eight rows w, w + 8, ...; all
+    // loads of them go out together
+    const bool cplx = bp.score == LEGEND_SCORE_COMPLEX, uses_rel = bp.score != LEGEND_SCORE_DOT;
+    const int k0 = lane, k1 = cplx ? lane + h : lane + 64;
+    const bool ok0 = cplx ? lane < h : lane < d;
+    const bool ok1 = cplx ? lane < h : lane + 64 < d;
+    const bool two = cplx || d > 64;          // uniform: the second column exists
+    struct RowVals { float x0, x1, y0, y1, r0, r1; };
+    auto load_rows = [&](int ids, RowVals (&v)[RPW]) __attribute__((always_inline)) {
+        const int c0 = ok0 ? k0 : 0, c1 = ok1 ? k1 : 0;
+#pragma unroll
+        for (int u = 0; u < RPW; ++u) {
+            const float* x = Ex + (int64_t)__builtin_amdgcn_readlane(ids, 3 * u + xcol) * d;
+            const float* y = Ey + (int64_t)__builtin_amdgcn_readlane(ids, 3 * u + ycol) * d;
+            v[u] = RowVals{x[c0], 0.f, y[c0], 0.f, 1.f, 1.f};
+            if (two) { v[u].x1 = x[c1]; v[u].y1 = y[c1]; }
+            if (uses_rel) {
+                const float* r = bp.E_rel + (int64_t)__builtin_amdgcn_readlane(ids, 3 * u + 1) * d;
+                v[u].r0 = r[c0];
+                if (two) v[u].r1 = r[c1];
+            }
+        }
+    };
+    auto compose = [&](const RowVals& v, float& q0, float& q1) __attribute__((always_inline)) {
+        if (bp.score == LEGEND_SCORE_DOT) { q0 = v.x0; q1 = v.x1; }
+        else if (bp.score == LEGEND_SCORE_DISTMULT) { q0 = v.x0 * v.r0; q1 = v.x1 * v.r1; }
+        else if (side == 0) { q0 = v.x0 * v.r0 - v.x1 * v.r1; q1 = v.x0 * v.r1 + v.x1 * v.r0; }
+        else                { q0 = v.r0 * v.x0 + v.r1 * v.x1; q1 = v.r0 * v.x1 - v.r1 * v.x0; }
+    };
+    {
+        RowVals v[RPW];
+        load_rows(eids, v);
+        {
+            const float* const rows[2] = {En + (int64_t)first_id[0] * d, En + (int64_t)first_id[1] * d};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) raw_load(rows, ks);
+            raw_load_tail(rows);
+        }
+        float f[RPW];
+#pragma unroll
+        for (int u = 0; u < RPW; ++u) {
+            const int row = w + kSWaves * u;
+            float q0, q1;
+            compose(v[u], q0, q1);
+            if (!ok0 || row >= nrows) q0 = 0.f;
+            if (!ok1 || row >= nrows) q1 = 0.f;
+            f[u] = (ok0 && row < nrows ? q0 * v[u].y0 : 0.f) + (ok1 && row < nrows ? q1 * v[u].y1 : 0.f);
+            if (cplx) {
+                if (ok0) { put(row, k0, q0); put(row, k1, q1); }
+                if (d + lane < 16 * NJ) put(row, d + lane, 0.f);
+            } else {
+                if (k0 < 16 * NJ) put(row, k0, q0);
+                if (k1 < 16 * NJ) put(row, k1, q1);
+            }
+        }
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1)
+#pragma unroll
+            for (int u = 0; u < RPW; ++u) f[u] += wave_shfl_xor(f[u], m);
+        if (lane == 0) {
+#pragma unroll
+            for (int u = 0; u < RPW; ++u) f_s[w + kSWaves * u] = f[u];
+        }
+    }
+    __syncthreads();
+
     // byte offsets of this lane's chunks in the composed rows: row 16 r + l15, chunk gq of a group of four (r even / odd)
     const int cr = chunk_cross(gq);
     const int qa[2] = {gq * (kSRow * 8) + ((l15 ^ cr) * 8), gq * (kSRow * 8) + (((16 + l15) ^ cr) * 8)};
@@ -449,7 +446,6 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
         float* const myref = Rw + w * kSRow;     // this wave's references
 #pragma unroll
         for (int k = 0; k < 16; ++k) sum[k] = 0.f;
-        gather(live(w) ? w : (w & 3) >> 1);
         f32v4 acc[4][2];
         auto mask_cols = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
@@ -465,25 +461,29 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
             return row16_max(fmaxf(acc[r][0][v], acc[r][1][v]));
         };
         auto next_of = [&](int i) __attribute__((always_inline)) { return live(i + kSWaves) ? i + kSWaves : (w & 3) >> 1; };      // last: the producer's first tile
-        int i = w;
-        if (live(i)) scores(next_of(i), acc);
-        if (w < 2) {
-            if (live(i)) mask_cols(i);
+        for (int i = w;; i += kSWaves) {
+            const bool here = live(i);
+            if (here) {
+                scores(next_of(i), acc);
+                mask_cols(i);
+            }
+            if (i < kSWaves) {                // every wave's first turn
+                if (w < 2) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+                    for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float m = live(i) ? row_max(r, v) : -1e30f;
-                    if (l15 == 0) mx_s[w * kSRow + 16 * r + 4 * gq + v] = m;
+                        for (int v = 0; v < 4; ++v) {
+                            const float m = here ? row_max(r, v) : -1e30f;
+                            if (l15 == 0) mx_s[w * kSRow + 16 * r + 4 * gq + v] = m;
+                        }
                 }
-        }
-        __syncthreads();
-        if (lane < kSRow) myref[lane] = lane < nrows ? fmaxf(mx_s[lane], mx_s[kSRow + lane]) : 1e30f;       // rows past the chunk: sums of 0
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        while (live(i)) {
-            mask_cols(i);
+                __syncthreads();
+                myref[lane] = lane < nrows ? fmaxf(mx_s[lane], mx_s[kSRow + lane]) : 1e30f;       // rows past the chunk: sums of 0
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            if (!here) break;
             float over = -1e30f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -525,8 +525,6 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
 #pragma unroll
                     for (int v = 0; v < 4; ++v) sum[4 * r + v] += exp_lifted(acc[r][nb][v] - ref[v]);
             }
-            i += kSWaves;
-            if (live(i)) scores(next_of(i), acc);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -568,7 +566,6 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
         __syncthreads();
         bad = flag_s[0] != 0u;                // uniform
     } else {
-        gather((w & 3) >> 1);
         if (tid < kSRow) a_s[tid] = LOSS == LEGEND_LOSS_LOGISTIC && tid < nrows ? -sigmoidf(-f_s[tid]) : 0.f;
     }
 
@@ -703,10 +700,8 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
                     }
             }
             __syncthreads();                             // everyone has its part of the composed rows
-            produce(0);
-            __syncthreads();
 #pragma unroll 1
-            for (int s = 1; s <= T64; ++s) {
+            for (int s = 0; s <= T64; ++s) {
                 if (s < T64) produce(s);
                 __syncthreads();
             }
@@ -857,6 +852,8 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
                 }
             }
         }
+        RowVals v[RPW];
+        load_rows(eids, v);                   // on their way across the barrier
         __syncthreads();
 
         // ---- epilogue: G_Q, chain rule, gradient rows of the positives ------------------------------------------------------
@@ -868,8 +865,6 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
         if (LOSS == LEGEND_LOSS_MARGIN) __syncthreads();
         const float* Gs = reinterpret_cast<const float*>(Qt);
         bool nan = false;
-        RowVals v[RPW];
-        load_rows(eids, v);
 #pragma unroll
         for (int u = 0; u < RPW; ++u) {
             const int row = w + kSWaves * u;
