@@ -245,11 +245,53 @@ k_long_plan(uint32_t* __restrict__ counters, const uint32_t* __restrict__ long_l
     }
 }
 
+// The same sum over at most LPR rows, by all LPR lanes of a group.  Bound by the chain row number -> gradient row: every lane brings one
+// row's number, so that the numbers cost one round trip to memory for all rows instead of one for every four.  Columns past d read the
+// row's first.  Four rows' loads go out together: eight need 106 registers a lane, and the kernel then no longer finds room beside
+// k_update (both sides of 50 000 edges, a million nodes, d = 100, from the long rows' first launch to their last: 460 us; four at 58
+// registers 138, as it was 144).
+// Long rows a batch, before and after: 15 000 nodes, 50 000 edges, both sides, d = 50: 240 and 184 us; 10 000 edges, d = 400: 79 and 70;
+// 120 000 nodes, 50 000 edges, d = 100: 98 and 94.
+template <int LPR, bool STREAM>
+__device__ inline void sum_group_rows(const float* __restrict__ grad, const uint32_t* __restrict__ sorted_vals, uint32_t lo,
+                                      uint32_t hi, int d, int c0, double acc[4]) {
+    const int n = hi > lo ? (int)(hi - lo) : 0;
+    const int l = threadIdx.x % LPR;
+    const uint32_t mine = l < n ? sorted_vals[lo + l] : 0u;
+    const int cc = c0 < d ? c0 : 0;
+    auto add = [&](auto&& load) {
+        for (int p = 0; p < n; p += 4) {
+            float v[4][4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) load(grad + (int64_t)__shfl(mine, min(p + k, n - 1), LPR) * d + cc, v[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[j] += p + k < n ? (double)v[k][j] : 0.0;
+        }
+    };
+    if ((d & 3) == 0) {
+        add([](const float* g, float (&v)[4]) {
+            const float4 x = row_load4<STREAM>(g);
+            v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+        });
+    } else if ((d & 1) == 0) {
+        const int second = cc + 2 < d ? 2 : 0;
+        add([second](const float* g, float (&v)[4]) {
+            const float2 x = row_load2<STREAM>(g), y = row_load2<STREAM>(g + second);
+            v[0] = x.x; v[1] = x.y; v[2] = y.x; v[3] = y.y;
+        });
+    } else {
+        const int o1 = cc + 1 < d ? 1 : 0, o2 = cc + 2 < d ? 2 : 0, o3 = cc + 3 < d ? 3 : 0;
+        add([o1, o2, o3](const float* g, float (&v)[4]) { v[0] = g[0]; v[1] = g[o1]; v[2] = g[o2]; v[3] = g[o3]; });
+    }
+}
+
 // One block per unit: the block's groups sum kUnit / GROUPS consecutive gradient rows each, the partial
 // sums are added in group order by the lanes of group 0, which get the unit's fp64 sum of columns cc..cc+3.
 template <int LPR, bool STREAM>
 __device__ inline void unit_sum(uint32_t lo_unit, uint32_t seg_hi, const uint32_t* __restrict__ sorted_vals,
-                                const float* __restrict__ grad, int d, int cbase, bool vec4, double* psum, double tot[4]) {
+                                const float* __restrict__ grad, int d, int cbase, double* psum, double tot[4]) {
     constexpr int GROUPS = 256 / LPR;
     constexpr int PER_GROUP = kUnit / GROUPS;
     const int gl = threadIdx.x / LPR;
@@ -258,7 +300,8 @@ __device__ inline void unit_sum(uint32_t lo_unit, uint32_t seg_hi, const uint32_
     const uint32_t lo = lo_unit + gl * PER_GROUP;
     const uint32_t hi = min(seg_hi, lo + PER_GROUP);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (cc < d && lo < hi) sum_rows<STREAM>(grad, sorted_vals, lo, hi, d, cc, vec4, acc);
+    static_assert(PER_GROUP <= LPR, "one row number per lane");
+    sum_group_rows<LPR, STREAM>(grad, sorted_vals, lo, hi, d, cc, acc);
 #pragma unroll
     for (int j = 0; j < 4; ++j) psum[(gl * LPR + col4) * 4 + j] = acc[j];
     __syncthreads();
@@ -273,7 +316,7 @@ __device__ inline void unit_sum(uint32_t lo_unit, uint32_t seg_hi, const uint32_
 }
 
 template <int LPR, bool STREAM>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 8)
 k_long_partial(const uint32_t* __restrict__ counters, const uint32_t* __restrict__ long_list,
                const uint32_t* __restrict__ unit_start, const uint32_t* __restrict__ seg_start,
                const uint32_t* __restrict__ sorted_vals, const float* __restrict__ grad, int d,
@@ -281,7 +324,6 @@ k_long_partial(const uint32_t* __restrict__ counters, const uint32_t* __restrict
     extern __shared__ double psum[];          // [GROUPS][4 * LPR]
     const int gl = threadIdx.x / LPR;
     const int col4 = threadIdx.x % LPR;
-    const bool vec4 = (d & 3) == 0;
     const uint32_t n_long = counters[2], n_units = counters[3];
     for (uint32_t unit = blockIdx.x; unit < n_units; unit += gridDim.x) {
         uint32_t a = 0, b = n_long;           // last r with unit_start[r] <= unit
@@ -294,7 +336,7 @@ k_long_partial(const uint32_t* __restrict__ counters, const uint32_t* __restrict
         for (int cbase = 0; cbase < d; cbase += 4 * LPR) {     // uniform trip count across the block
             const int cc = cbase + col4 * 4;
             double tot[4];
-            unit_sum<LPR, STREAM>(seg_lo + (unit - unit_start[a]) * kUnit, seg_hi, sorted_vals, grad, d, cbase, vec4, psum, tot);
+            unit_sum<LPR, STREAM>(seg_lo + (unit - unit_start[a]) * kUnit, seg_hi, sorted_vals, grad, d, cbase, psum, tot);
             if (gl == 0 && cc < d)
                 for (int j = 0; j < 4 && cc + j < d; ++j) partial[(int64_t)unit * d + cc + j] = tot[j];
         }
@@ -379,7 +421,7 @@ k_update_small(const uint32_t* __restrict__ counters, const uint32_t* __restrict
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         for (uint32_t lo = seg_lo; lo < seg_hi; lo += kUnit) {
             double tot[4];
-            unit_sum<LPR, false>(lo, seg_hi, sorted_vals, grad, d, cbase, vec4, psum, tot);
+            unit_sum<LPR, false>(lo, seg_hi, sorted_vals, grad, d, cbase, psum, tot);
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[j] += tot[j];
         }
