@@ -13,10 +13,11 @@
 // The operand that is transposed comes out of the same LDS tile by the transposing read.  The weights' order of registers after a score
 // product is already the order of an operand with the positives as contraction index.
 //
-// What bounds it: instruction issue (two waves a SIMD, one vector instruction per wave and five cycles) and the matrix pipe, which needs
-// 130 us of a batch of 50 000 edges, 1000 negatives, d = 100; memory is read twice, 1.1 GB.  That batch takes 0.50 ms by itself, 0.54 with
-// fp32 instructions and a single sweep; both sides and complex products 1.14 (1.29).  Against the two-sweep kernel on fp32 instructions:
-// d = 50, both sides, chunks of 100, 0.61 ms (0.95); logistic at d = 128, 20 011 edges, 333 negatives, 0.137 ms (0.24).
+// What bounds it: issue and latency at two waves a SIMD (a wave issues one vector instruction per five cycles; the producers' chain sets the
+// pace of sweep 2).  The matrix pipe needs 130 us of a batch of 50 000 edges, 1000 negatives, d = 100, and is busy a quarter of the
+// time; memory is read twice, 1.1 GB.  That batch takes 0.49 ms by itself, 0.54 with
+// fp32 instructions and a single sweep; both sides and complex products 0.98 (1.29).  Against the two-sweep kernel on fp32 instructions:
+// d = 50, both sides, chunks of 100, 0.56 ms (0.95); logistic at d = 128, 20 011 edges, 333 negatives, 0.131 ms (0.24).
 // Against 64 bits the gradients are closer than with fp32 instructions (2-norm over one batch, 14 shapes of d = 8 to 128 and all four losses,
 // three seeds each: geometric mean 6.7e-8, 8.1e-8 before; 39 of 42 smaller, the others at scores in the tens).
 //

@@ -421,6 +421,7 @@ int stage_edges(legend_ctx* c, int i, int j, const int32_t* edges, int64_t m, in
 // by total: d = 100, 99 to 214 MB 1 to 4 % more, 252 MB 1 % more, 290 MB 1 % less, 443 MB (1M rows of tables and more: 1.2 GB) 2 %
 // (3 %) less; d = 64, 208 MB 1 % more, 256 MB 4 % less, 354 MB 6 % less; d = 50 (200-byte rows), 56 MB 4 % and 182 MB
 // 5 % more, 269 MB 1 % less; wide path d = 400, 158 MB 1 % more, 267 MB 2 %, 320 MB 4 %, 480 MB 8 % less.
+// (Figures with k_chunk's marked stores; k_chunk_split never marks its stores, which are pieces of lines, so there the update's loads alone.)
 int32_t streams_rows(const legend_ctx* c, int i, int j, int64_t m) {
     constexpr int64_t kCacheBytes = (int64_t)256 << 20;
     const BatchGeom g = make_geom(c, (int)std::min<int64_t>(m, c->cfg.batch_size));
