@@ -43,6 +43,7 @@ constexpr int kSRow = 64;                   // positives per workgroup (padded),
 constexpr int kSWPart = 16 * kSRow * 8;     // bytes of one part of a weight tile
 constexpr int kSWTile = 3 * kSWPart;
 constexpr float kSLiftLn = 58.f * 0.693147180559945309f;
+constexpr float kSMasked = -1e30f;          // score of a column past the chunk's negatives
 
 // exp(x) * 2^-58 for x <= 110 without overflow: 2^(h/2) is scaled by 2^-29 and squared.
 __device__ inline float exp_lifted(float x) {
@@ -455,7 +456,7 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[r][nb][v] = ok ? acc[r][nb][v] : -1e30f;
+                    for (int v = 0; v < 4; ++v) acc[r][nb][v] = ok ? acc[r][nb][v] : kSMasked;
             }
         };
         auto row_max = [&](int r, int v) __attribute__((always_inline)) {
@@ -474,7 +475,7 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
                     for (int r = 0; r < 4; ++r)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            const float m = here ? row_max(r, v) : -1e30f;
+                            const float m = here ? row_max(r, v) : kSMasked;
                             if (l15 == 0) mx_s[w * kSRow + 16 * r + 4 * gq + v] = m;
                         }
                 }
@@ -554,9 +555,10 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
             }
             const float neg_sum = total;
             if (bp.softmax_with_pos && in) total += exp_lifted(f - m);
-            // no reference exceeds its row's largest term, which therefore contributes at least 2^-58: the sum can only leave
-            // this range if a score is not finite
-            if (in && !(total > 1e-30f && total < 1e36f)) flag_s[0] = 1u;
+            // above a masked column's value no reference exceeds its row's largest term, which therefore contributes at least
+            // 2^-58: the sum can only leave this range if a score is not finite.  Where no score lies above that value the
+            // reference is the masked columns', which were then counted: left to the fp32 kernel as well.
+            if (in && (!(total > 1e-30f && total < 1e36f) || m <= kSMasked)) flag_s[0] = 1u;
             // the log-sum-exp in two floats: weights are exp((S - ref) - low); rows past the chunk: weight 0
             const double lse = (double)m + (log((double)total) + 58.0 * 0.693147180559945309);
             ref_s[tid] = in ? (float)lse : 1e30f;

@@ -1,0 +1,51 @@
+"""Losses of the batch kernel on bf16 parts (product scores up to 128 dimensions) at the ends of what its sums hold."""
+
+import numpy as np
+import pytest
+
+from oracle.bucket import OracleConfig, Tables, batch_gradients
+from tests.parity_util import kappa_for
+
+pytestmark = pytest.mark.gpu
+
+DOT = 0
+SOFTMAX, LOGISTIC, SOFTMAX_POS, MARGIN = 0, 1, 2, 3
+
+
+def _batch(node, edges, *, C, N, loss, seed=3, **kw):
+    """One batch of the bucket between the two halves of the nodes, destinations corrupted: the library's loss, the oracle's loss, and
+    the states (squares of the gradients)."""
+    from paper_2505_09258_amd import binding as L
+    V, d = node.shape
+    args = dict(num_nodes=V, num_relations=0, dim=d, num_partitions=2, batch_size=edges.shape[0], chunk_size=C, num_negs=N,
+                score=DOT, loss=loss, seed=seed, **kw)
+    ctx = L.legend_init_partitions(L.make_config(**args), node, None)
+    try:
+        for p in range(2):
+            L.legend_swap_partition(ctx, -1, p)
+        L.legend_profile_enable(ctx, 0xffffffff)
+        got = L.legend_train_bucket(ctx, 0, 1, edges)["loss_sum"]
+        launches = {k: v["launches"] for k, v in L.legend_profile_read(ctx).items()}
+        state = L.legend_read_embeddings(ctx, L.TABLE_NODE_STATE, None, V, d)
+    finally:
+        L.legend_destroy(ctx)
+    assert launches["chunk_redo"] == 1                     # the launch behind the kernel on bf16 parts
+    cfg = OracleConfig(**args)
+    want, _, _ = batch_gradients(Tables(cfg, node, None), 0, 1, edges, 0, 0)
+    return got, want, state
+
+
+@pytest.mark.parametrize("d,N", [(33, 200), (100, 70), (128, 130), (40, 600)])
+@pytest.mark.parametrize("loss", [SOFTMAX, SOFTMAX_POS])
+def test_scores_far_below_any_finite_mask(d, N, loss):
+    """All scores finite, between -1e34 and -1e32, in tiles with columns past the negatives: none of those may count."""
+    rng = np.random.default_rng(d)
+    V, B, C = 1_000, 64, 32
+    node = (1e16 * (1.0 + rng.random((V, d)))).astype(np.float32)
+    node[V // 2:] *= -1
+    edges = np.stack([rng.integers(0, V // 2, B), np.zeros(B, np.int64), rng.integers(0, V // 2, B)], 1).astype(np.int32)
+    got, want, state = _batch(node, edges, C=C, N=N, loss=loss)
+    # scores 1e30 and more apart: the loss is a sum of differences of scores, each off by a few roundings of its own size, 4e32 d at
+    # most (a weight is 0, 1 or a power of the rounding of its score: not asked for)
+    assert abs(got - want) <= 1e-5 * abs(want) + B * kappa_for(d, "loss") * 4e32 * d
+    assert np.isfinite(state).all()
