@@ -139,7 +139,7 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
     float* f_s = reinterpret_cast<float*>(Wt + 2 * kSWTile);      // [64] positive scores
     float* ref_s = f_s + kSRow;
     float* low_s = ref_s + kSRow;             // [64] log-sum-exp: ref_s + low_s
-    float* lse_s = low_s + kSRow;             // [64] log-sum-exp - f
+    float* lse_s = low_s + kSRow;             // [64] loss of the row: log-sum-exp - f
     float* a_s = lse_s + kSRow;               // [64] dL/df
     float* rowloss_s = a_s + kSRow;           // [64]
     float* Lw = rowloss_s + kSRow;            // [8][64] every wave's row sums (margin: counts)
@@ -563,7 +563,11 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
             const double lse = (double)m + (log((double)total) + 58.0 * 0.693147180559945309);
             ref_s[tid] = in ? (float)lse : 1e30f;
             low_s[tid] = in ? (float)(lse - (double)(float)lse) : 0.f;
-            lse_s[tid] = in ? (m - f) + (logf(total) + kSLiftLn) : 0.f;
+            float row_loss = (m - f) + (logf(total) + kSLiftLn);
+            // with the positive score in the sum the loss is softplus(log-sum-exp of the negatives - f): where the positive
+            // dominates, lse - f cancels
+            if (bp.softmax_with_pos) row_loss = softplusf((float)((double)m - (double)f + (log((double)neg_sum) + 58.0 * 0.693147180559945309)));
+            lse_s[tid] = in ? row_loss : 0.f;
             a_s[tid] = in ? -neg_sum / total : 0.f;
         }
         __syncthreads();

@@ -3,6 +3,7 @@
 import numpy as np
 import pytest
 
+from oracle import negatives
 from oracle.bucket import OracleConfig, Tables, batch_gradients
 from tests.parity_util import kappa_for
 
@@ -49,3 +50,20 @@ def test_scores_far_below_any_finite_mask(d, N, loss):
     # most (a weight is 0, 1 or a power of the rounding of its score: not asked for)
     assert abs(got - want) <= 1e-5 * abs(want) + B * kappa_for(d, "loss") * 4e32 * d
     assert np.isfinite(state).all()
+
+
+@pytest.mark.parametrize("d,N", [(33, 200), (64, 50), (100, 333), (128, 130)])
+@pytest.mark.parametrize("f", [12.0, 30.0, 75.0])
+def test_dominating_positive_score(d, N, f):
+    """Scores of zero and positive scores of f: the loss of a row is log(1 + N exp(-f)), far below the rounding of f."""
+    V, B, C = 4_000, 100, 50
+    node = np.zeros((V, d), np.float32)
+    edges = np.stack([np.arange(B) % 50, np.zeros(B, np.int64), np.arange(B) % 50], 1).astype(np.int32)
+    cfg = OracleConfig(num_nodes=V, num_relations=0, dim=d, num_partitions=2, batch_size=B, chunk_size=C, num_negs=N, score=DOT, seed=3)
+    free = np.setdiff1d(np.arange(V // 2), negatives.batch_negatives(cfg, 0, 0, 1, 0, edges, edges))[:50]
+    edges[:, 2] = free[edges[:, 2]]                  # uniform negatives do not depend on the edges
+    node[:50, 3], node[V // 2 + free, 3] = 2.0, f / 2.0
+    got, _, _ = _batch(node, edges, C=C, N=N, loss=SOFTMAX_POS)
+    want = B * np.log1p(N * np.exp(-f))              # (a log-sum-exp less f cancels in 64 bits too)
+    # x = log N - f is taken in double and rounded once (2^-24 of x, at most f, is the relative change of exp(x)); exp, log1p: some ulp
+    assert abs(got - want) <= (f + 16) * 2.0 ** -24 * want
