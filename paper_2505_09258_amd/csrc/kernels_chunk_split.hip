@@ -42,7 +42,6 @@ constexpr int kSWaves = kSThreads / kWave;
 constexpr int kSRow = 64;                   // positives per workgroup (padded), and negatives per step
 constexpr int kSWPart = 16 * kSRow * 8;     // bytes of one part of a weight tile
 constexpr int kSWTile = 3 * kSWPart;
-constexpr float kSLiftLn = 58.f * 0.693147180559945309f;
 constexpr float kSMasked = -1e30f;          // score of a column past the chunk's negatives
 
 // exp(x) * 2^-58 for x <= 110 without overflow: 2^(h/2) is scaled by 2^-29 and squared.
@@ -560,13 +559,15 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
             // reference is the masked columns', which were then counted: left to the fp32 kernel as well.
             if (in && (!(total > 1e-30f && total < 1e36f) || m <= kSMasked)) flag_s[0] = 1u;
             // the log-sum-exp in two floats: weights are exp((S - ref) - low); rows past the chunk: weight 0
-            const double lse = (double)m + (log((double)total) + 58.0 * 0.693147180559945309);
+            constexpr double lift = 58.0 * 0.693147180559945309;
+            const double lse = (double)m + (log((double)total) + lift);
             ref_s[tid] = in ? (float)lse : 1e30f;
             low_s[tid] = in ? (float)(lse - (double)(float)lse) : 0.f;
-            float row_loss = (m - f) + (logf(total) + kSLiftLn);
-            // with the positive score in the sum the loss is softplus(log-sum-exp of the negatives - f): where the positive
-            // dominates, lse - f cancels
-            if (bp.softmax_with_pos) row_loss = softplusf((float)((double)m - (double)f + (log((double)neg_sum) + 58.0 * 0.693147180559945309)));
+            // The loss rounded once: the logarithm of a sum that is 2^-58 times too small, and the lift's, are both near 40, and their
+            // roundings in fp32 were the larger part of the loss's error (a bias of 3e-8 of a loss of 7).  With the positive
+            // score in the sum the loss is softplus(log-sum-exp of the negatives - f): where the positive dominates, lse - f cancels.
+            float row_loss = (float)(lse - (double)f);
+            if (bp.softmax_with_pos) row_loss = softplusf((float)(((double)m - (double)f) + (log((double)neg_sum) + lift)));
             lse_s[tid] = in ? row_loss : 0.f;
             a_s[tid] = in ? -neg_sum / total : 0.f;
         }

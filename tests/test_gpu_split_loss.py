@@ -67,3 +67,13 @@ def test_dominating_positive_score(d, N, f):
     want = B * np.log1p(N * np.exp(-f))              # (a log-sum-exp less f cancels in 64 bits too)
     # x = log N - f is taken in double and rounded once (2^-24 of x, at most f, is the relative change of exp(x)); exp, log1p: some ulp
     assert abs(got - want) <= (f + 16) * 2.0 ** -24 * want
+
+
+@pytest.mark.parametrize("d,N", [(33, 200), (100, 1000), (128, 333), (64, 61)])
+def test_loss_of_equal_scores(d, N):
+    """Scores of zero: every row's loss is log N, rounded to fp32 (2^-24; the logarithm is taken in double)."""
+    B = 100
+    edges = np.stack([np.arange(B), np.zeros(B, np.int64), np.arange(B)], 1).astype(np.int32)
+    got, _, state = _batch(np.zeros((2_000, d), np.float32), edges, C=50, N=N, loss=SOFTMAX)
+    assert abs(got - B * np.log(N)) <= 2.0 ** -24 * B * np.log(N)
+    assert not state.any()
