@@ -77,3 +77,20 @@ def test_loss_of_equal_scores(d, N):
     got, _, state = _batch(np.zeros((2_000, d), np.float32), edges, C=50, N=N, loss=SOFTMAX)
     assert abs(got - B * np.log(N)) <= 2.0 ** -24 * B * np.log(N)
     assert not state.any()
+
+
+@pytest.mark.parametrize("d", [50, 100, 101, 112, 128])
+def test_loss_over_many_scores_has_no_bias(d):
+    """Positive scores of zero and no margin: the loss is the sum of the scores above zero, 400 000 of them.  Roundings of either sign
+    average out (3 x 2^-24 of a score's root mean square each: 1e-9 of the sum); a mean of an eighth of 2^-24 of a score stays whole
+    (9e-9 of the sum), and half of that is the bar."""
+    rng = np.random.default_rng(d)
+    V, B, N = 4_000, 800, 1_000
+    node = (0.3 * rng.standard_normal((V, d))).astype(np.float32)
+    node[V // 2:V // 2 + 100] = 0
+    edges = np.stack([rng.integers(0, V // 2, B), np.zeros(B, np.int64), rng.integers(0, 100, B)], 1).astype(np.int32)
+    errors = []
+    for seed in range(4):
+        got, want, _ = _batch(node, edges, C=50, N=N, loss=MARGIN, margin=0.0, seed=seed)
+        errors.append((got - want) / want)
+    assert abs(np.mean(errors)) <= 4.5e-9, errors
