@@ -800,7 +800,6 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
 #pragma unroll
                             for (int r0 = 0; r0 < R; r0 += 2) {
                                 f32v4 t[2] = {f32v4{0.f, 0.f, 0.f, 0.f}, f32v4{0.f, 0.f, 0.f, 0.f}};
-                                if (!LOW) { t[0] = acc[b][r0]; t[1] = acc[b][r0 + 1]; }
 #pragma unroll
                                 for (int pp = 0; pp < 6; ++pp)
 #pragma unroll
@@ -810,7 +809,10 @@ k_chunk_split(BatchGeom g, BucketParams bp, const int32_t* __restrict__ neg_ids,
                                         t[r] = mfma_bf16(x, y, t[r]);
                                     }
 #pragma unroll
-                                for (int r = 0; r < 2; ++r) acc[b][r0 + r] = LOW ? acc[b][r0 + r] + t[r] : t[r];
+                                for (int r = 0; r < 2; ++r) {
+                                    acc[b][r0 + r] += t[r];
+                                    asm volatile("" : "+v"(acc[b][r0 + r]));      // added here: put off, the sums of a step fill the registers
+                                }
                             }
                         }
                     }
