@@ -50,3 +50,19 @@ def test_sums_of_one_sign(d, N, loss):
     roundings = 2.0 * (N / 288) ** 0.5 + (4.0 if loss == LOGISTIC else 0.0)
     error = np.linalg.norm(got - want) / np.linalg.norm(want)
     assert error <= roundings * 2.0 ** -24, error * 2.0 ** 24
+
+
+@pytest.mark.parametrize("d,N,std", [(20, 700, 2.5), (64, 600, 1.3), (100, 1_000, 1.05), (128, 1_000, 0.95)])
+@pytest.mark.parametrize("loss", [SOFTMAX, SOFTMAX_POS], ids=["softmax", "softmax_pos"])
+def test_copies_of_a_dominating_negative(d, N, std, loss):
+    """Every source row stands several times among the negatives, with a score that lies 50 to 150 above the rest: some waves raise their
+    references for a row of their tile above 110, others keep theirs, and the sums of either belong together."""
+    rng = np.random.default_rng(d)
+    V, B, C = 600, 300, 50
+    node = (std * rng.standard_normal((V, d))).astype(np.float32)
+    node[V // 2:] = node[:V // 2]
+    edges = np.stack([rng.permutation(V // 2)[:B], np.zeros(B, np.int64), rng.integers(0, V // 2, B)], 1).astype(np.int32)
+    got, want = _source_rows(node, edges, C=C, N=N, loss=loss)
+    # weights that do not add up to 1 to fp32's precision are off by 2^-24 times a score (256 or so at most), and as much for their sum
+    bound = 2.0 ** -24 * 512 * np.abs(node).max()
+    assert np.abs(got - np.abs(want)).max() <= bound, np.abs(got - np.abs(want)).max() / bound
