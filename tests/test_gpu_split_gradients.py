@@ -66,3 +66,25 @@ def test_copies_of_a_dominating_negative(d, N, std, loss):
     # weights that do not add up to 1 to fp32's precision are off by 2^-24 times a score (256 or so at most), and as much for their sum
     bound = 2.0 ** -24 * 512 * np.abs(node).max()
     assert np.abs(got - np.abs(want)).max() <= bound, np.abs(got - np.abs(want)).max() / bound
+
+
+@pytest.mark.parametrize("d,N,std", [(32, 600, 1.6), (64, 600, 1.2), (96, 1_000, 1.0), (100, 1_000, 1.0), (104, 1_000, 0.95), (128, 1_000, 0.85)])
+@pytest.mark.parametrize("loss", [SOFTMAX, SOFTMAX_POS], ids=["softmax", "softmax_pos"])
+def test_weight_of_a_dominating_negative(d, N, std, loss):
+    """Every source row stands among the destinations too: as a negative its score is near 100, where the others, the softmax reference
+    among them, are in the tens.  Its weight is 1, and the gradient the row less the destination's."""
+    rng = np.random.default_rng(d)
+    V, B, C = 2_000, 400, 50
+    node = (std * rng.standard_normal((V, d))).astype(np.float32)
+    node[V // 2:] = node[:V // 2]
+    edges = np.stack([rng.permutation(V // 2)[:B], np.zeros(B, np.int64), rng.integers(0, V // 2, B)], 1).astype(np.int32)
+    got, want = _source_rows(node, edges, C=C, N=N, loss=loss)
+    source = node[np.sort(edges[:, 0])].astype(np.float64)
+    destination = node[edges[np.argsort(edges[:, 0]), 2]]
+    alone = np.abs(want - (source - destination)).max(axis=1) < 1e-8        # the weight is 1 to 64 bits, as good as
+    assert alone.sum() > 50
+    # the weight: the row's sum in two exponentials squared and a few additions, the logarithm of it in 64 bits and rounded to 48, one
+    # exponential: some eight roundings, of the source row; one each of the difference and of the root of the state
+    allowed = 2.0 ** -24 * (8.0 * np.abs(source[alone]) + 2.0 * np.abs(want[alone])) + 1e-8
+    share = np.abs(got[alone] - np.abs(want[alone])) / allowed
+    assert share.max() <= 1.0, share.max()
