@@ -363,6 +363,12 @@ def run_resident(args, w, K, W, L, graphs, torch, np, *, kernels_pass=True, cpu_
     uniq, nbatches = L.legend_unique_rows_read(ctx)
     fallback = L.legend_fallback_chunks_read(ctx)
     assert nbatches == K, (nbatches, K)
+    # which kernel that was: a launch over flagged workgroups follows the one on bf16 parts, and no other (one more batch, untimed)
+    L.legend_profile_enable(ctx, 1 << names.index("chunk_redo"))
+    i, j, b0, _, ep = work[-1]
+    run([(i, j, b0, b0 + 1, ep)])
+    split = w.dim > 128 or L.legend_profile_read(ctx)["chunk_redo"]["launches"] > 0
+    L.legend_profile_enable(ctx, chunk_bit)
     edges_per_s = K * B / wall
     log(f"[bench] {w.name}: {K} steps: wall {wall * 1e3:.1f} ms, device {dev_ms:.1f} ms, {edges_per_s:.3e} edges/s")
 
@@ -376,9 +382,6 @@ def run_resident(args, w, K, W, L, graphs, torch, np, *, kernels_pass=True, cpu_
     Q = sides * (-(-P // w.chunk_size)) * N
     u_b = uniq / max(nbatches, 1)
     alg_bytes = 12 * P + 4 * Q + 4 * d * (2 * P + Q) + 16 * d * u_b
-    small = shape["occurrences"] <= 4096
-    split = w.dim > 128 or (args.update_mode != "atomic" and os.environ.get("LEGEND_NO_FAST_CHUNK") != "1" and
-                            (N * d >= 5000 or (N * d >= 2500 and d > 32 and (w.loss == graphs.LOSS_SOFTMAX or small))))
     kname = ("k_gemm_compose/scores/rowstats/gq/gneg/chain (one launch each)" if w.dim > 128
              else ("k_chunk_split" if split else "k_chunk"))
     traffic = TRAFFIC_BYTES.get(w.name.split("+")[0], {}) if kname == "k_chunk_split" else {}

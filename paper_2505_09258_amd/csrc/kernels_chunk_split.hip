@@ -1009,15 +1009,22 @@ template <> hipError_t launch_split_nj<6>(hipStream_t, const BatchGeom&, const B
 template <> hipError_t launch_split_nj<7>(hipStream_t, const BatchGeom&, const BucketParams&, const Workspace&);
 template <> hipError_t launch_split_nj<8>(hipStream_t, const BatchGeom&, const BucketParams&, const Workspace&);
 
-// Little work per workgroup stays with k_chunk: there the second launch over flagged workgroups and the second workgroup that fits a
-// compute unit weigh more than the products.  Time of a batch with this kernel over that of k_chunk by negatives x dimension: 64 x 32 1.16,
-// 100 x 10 1.03, 33 x 70 1.03, 100 x 32 1.04, 40 x 100 (logistic, 10 000 edges) 1.04, 300 x 16 1.01; 30 x 100 0.93 and 64 x 100 0.93 (softmax, up to
-// 1000 edges), 64 x 50 0.99, 64 x 100 (logistic, 600 edges) 0.88, 30 x 128 0.83; from 200 x 100 on 0.5 to 0.9.
+// Little work per workgroup stays with k_chunk.  Time of a batch with this kernel over that of k_chunk (Dot, one side, chunks of 50; edges:
+// loss negatives x dimension ratio), each the smaller of two runs in turn:
+// Batches of up to kSmallSortMax gradient rows, whose index sides are made in groups: a batch is its kernels one behind the other, and
+// the longest is this one.  500: softmax 30 x 100 0.92, 64 x 100 0.91, 40 x 64 0.96, 60 x 50 0.92, 25 x 128 0.79; logistic 0.86, -, 0.94, 0.92,
+// 0.80; margin 0.83, -, 0.87, 0.87, 0.74.  Not at 100 x 32: softmax 1.00, logistic 1.04; 156 x 32 0.91, 0.99.
+// Larger batches cost some 25 launches, which bound them up to some 8 000 edges (100 us): the second launch over flagged workgroups
+// is then 5 us more, and two workgroups of k_chunk fit a compute unit.  2 500: softmax 100 x 50 1.01, 200 x 50 1.06, 100 x 100 0.97, 400 x 50 0.94,
+// 100 x 128 1.04, 200 x 128 0.99; logistic 1.03, 1.03, 1.04, 0.91, 1.03, 1.02.  25 000: softmax 100 x 50 1.02, 64 x 100 1.03, 128 x 100 0.97, 64 x 128
+// 1.13, 300 x 100 0.88; logistic 250 x 40 0.99, 64 x 100 1.06, 128 x 100 1.03, 300 x 100 1.00, 64 x 128 1.14, 100 x 128 1.10, 200 x 128 0.97, 333 x
+// 128 0.90; margin 64 x 100 0.97, 128 x 100 0.92, 100 x 128 1.06, 200 x 128 0.93.
 bool chunk_split_applies(const BatchGeom& g, const BucketParams& bp) {
     if (bp.atomic_mode != 0 || bp.score == LEGEND_SCORE_TRANSE_L1 || bp.dim > kNarrowMaxDim) return false;
     if (g.N > (1 << 20)) return false;        // a chunk's gradient rows are addressed by 32 bits
     const int64_t work = (int64_t)g.N * bp.dim;
-    return work >= 5000 || (work >= 2500 && bp.dim > 32 && (bp.loss == LEGEND_LOSS_SOFTMAX || g.n_occ <= kSmallSortMax));
+    if (g.n_occ <= kSmallSortMax) return work >= (bp.dim > 32 ? 2500 : 5000);
+    return work >= (bp.dim <= 100 ? 10000 : 16000);
 }
 
 hipError_t launch_chunks_split(hipStream_t st, const BatchGeom& g, const BucketParams& bp, const Workspace& ws) {

@@ -72,3 +72,32 @@ def test_infinite_rows(loss, where, d, C, N):
     with np.errstate(all="ignore"):
         allowed = 2.0 * np.abs(g) * off + off ** 2
     assert (np.abs(state[fine].astype(np.float64) - want[fine]) <= STATE_RTOL * want[fine] + allowed[fine]).all()
+
+
+def _launches(loss, d, N, B, **kw):
+    from paper_2505_09258_amd import binding as L
+    V = 3_000
+    rng = np.random.default_rng(d)
+    edges = np.stack([rng.integers(0, V, B), np.zeros(B, np.int64), rng.integers(0, V, B)], 1).astype(np.int32)
+    ctx = L.legend_init_partitions(L.make_config(num_nodes=V, dim=d, batch_size=B, chunk_size=50, num_negs=N, score=DOT, loss=loss,
+                                                 seed=1, **kw), np.full((V, d), 0.01, np.float32), None)
+    try:
+        L.legend_swap_partition(ctx, -1, 0)
+        L.legend_profile_enable(ctx, 0xffffffff)
+        L.legend_train_bucket(ctx, 0, 0, edges)
+        return {k: v["launches"] for k, v in L.legend_profile_read(ctx).items()}
+    finally:
+        L.legend_destroy(ctx)
+
+
+# 500 edges and 10 chunks of up to 300 negatives are at most 4096 gradient rows, 2 500 edges are more
+@pytest.mark.parametrize("d,N,B,split", [(32, 78, 500, False), (36, 70, 500, True), (128, 19, 500, False), (128, 20, 500, True),
+                                         (32, 156, 500, False), (32, 157, 500, True), (100, 64, 500, True),
+                                         (100, 99, 2_500, False), (100, 100, 2_500, True), (50, 199, 2_500, False),
+                                         (128, 124, 2_500, False), (128, 125, 2_500, True), (101, 158, 2_500, False)])
+@pytest.mark.parametrize("loss", [SOFTMAX, LOGISTIC, MARGIN], ids=["softmax", "logistic", "margin"])
+def test_which_kernel_runs(loss, d, N, B, split):
+    """Few negatives of few dimensions are for the fp32 kernel, fewer in small batches, whatever the loss; a launch over flagged
+    workgroups follows the kernel on bf16 parts only."""
+    launches = _launches(loss, d, N, B)
+    assert launches["chunk"] == 1 and launches["chunk_redo"] == (1 if split else 0)
