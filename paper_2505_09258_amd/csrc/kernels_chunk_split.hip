@@ -116,7 +116,6 @@ __device__ __forceinline__ uint4 join(uint2 a, uint2 b) { return make_uint4(a.x,
 template <int NJ>
 struct SplitShape {
     static constexpr bool packed_tail = NJ == 7;            // d = 97..100: three slices of 32 and four elements more
-    static constexpr int d_min = NJ == 7 ? 97 : NJ == 8 ? 101 : 16 * NJ - 31;
     static constexpr int KS = NJ / 2;                       // slices of 32 contraction elements
     static constexpr int NCH = 4 * NJ;
     static constexpr int q_part = NCH * kSRow * 8;

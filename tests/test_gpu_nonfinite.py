@@ -14,8 +14,9 @@ DOT, TRANSE = 0, 3
 LOGISTIC, SOFTMAX_POS, MARGIN, DST = 1, 2, 3, 0
 
 
-def _one_batch(node, rel, edges, *, C, N, seed, **kw):
-    """The states after one batch of all edges (zero before: squares of the gradients) and the negatives per chunk."""
+def _one_batch(node, rel, edges, *, C, N, seed, on_parts=None, **kw):
+    """The states after one batch of all edges (zero before: squares of the gradients) and the negatives per chunk.  on_parts: whether
+    the batch has to have run on the kernel on bf16 parts, where that matters."""
     from paper_2505_09258_amd import binding as L
     V, d = node.shape
     B = edges.shape[0]
@@ -24,7 +25,11 @@ def _one_batch(node, rel, edges, *, C, N, seed, **kw):
     ctx = L.legend_init_partitions(cfg, node, rel)
     try:
         L.legend_swap_partition(ctx, -1, 0)
+        if on_parts is not None:
+            L.legend_profile_enable(ctx, 0xffffffff)
         L.legend_train_bucket(ctx, 0, 0, edges)
+        if on_parts is not None:                   # the launch over flagged workgroups follows that kernel only
+            assert L.legend_profile_read(ctx)["chunk_redo"]["launches"] == (1 if on_parts else 0)
         state = L.legend_read_embeddings(ctx, L.TABLE_NODE_STATE, None, V, d)
     finally:
         L.legend_destroy(ctx)

@@ -38,17 +38,17 @@ CASES = [
     _case("distmult_d400_both", DISTMULT, SOFTMAX, BOTH, 3_000, 45, 400, 1, 0, 0, 400, 100, 130, 0, 900, 0.15),
     _case("complex_d132_offdiag", COMPLEX, SOFTMAX, BOTH, 2_000, 7, 132, 2, 1, 0, 150, 40, 33, 8, 320, 0.3),
     _case("dot_d512_logistic", DOT, LOGISTIC, SRC, 800, 0, 512, 1, 0, 0, 96, 32, 64, 0, 200, 0.1),
-    # d = 64 through the single-sweep kernel: all eight steps of negatives with a ragged tail, partial last chunk
+    # d = 64: sixteen tiles of 64 negatives, the last one ragged, and a partial last chunk
     _case("complex_d64_n1000_both", COMPLEX, SOFTMAX, BOTH, 9_000, 5, 64, 2, 0, 1, 700, 50, 1_000, 300, 1_530, 0.3),
-    # d = 100 with the largest negative count and full 64-row chunks (single-sweep kernel, all eight steps)
+    # d = 100 with sixteen whole tiles of negatives and full 64-row chunks
     _case("distmult_d100_n1024", DISTMULT, SOFTMAX, SRC, 8_000, 11, 100, 2, 1, 0, 640, 64, 1_024, 100, 1_500, 0.3),
-    # Eq. 1 with the positive score inside the log-sum-exp, through each of the three chunk kernels
+    # Eq. 1 with the positive score inside the log-sum-exp, through the kernel on bf16 parts (d = 100, 48) and the wide path
     _case("complex_d100_softmax_pos", COMPLEX, SOFTMAX_POS, BOTH, 5_000, 9, 100, 2, 0, 1, 600, 50, 200, 40, 1_300, 0.3),
     _case("dot_d48_softmax_pos", DOT, SOFTMAX_POS, DST, 3_000, 0, 48, 1, 0, 0, 500, 64, 100, 0, 1_100, 0.3),
     _case("distmult_d256_softmax_pos", DISTMULT, SOFTMAX_POS, SRC, 2_000, 5, 256, 1, 0, 0, 200, 40, 70, 0, 450, 0.2),
     # a wide dimension that is not a multiple of four (rows only 8-byte aligned); chunks of 120 rows take two row tiles
     _case("complex_d150_both", COMPLEX, SOFTMAX, BOTH, 2_500, 6, 150, 2, 1, 0, 300, 120, 90, 20, 700, 0.2),
-    # d = 100 with chunks of 100 edges: the single-sweep kernel with two 50-row tiles per chunk (the dimension sweep's shape)
+    # d = 100 with chunks of 100 edges: two 50-row tiles per chunk (the dimension sweep's shape)
     _case("distmult_d100_two_row_tiles", DISTMULT, SOFTMAX, BOTH, 6_000, 7, 100, 2, 0, 1, 700, 100, 300, 30, 1_500, 0.3),
     # translational score (vector-ALU kernel): both sides, a dimension that is no multiple of four, two row tiles per chunk
     _case("transe_d100_both", TRANSE, SOFTMAX, BOTH, 5_000, 9, 100, 2, 0, 1, 600, 50, 200, 40, 1_300, 0.1),
@@ -58,7 +58,7 @@ CASES = [
     # segments and plans (hub rows included); one edge more and the multi-kernel sort takes over
     _case("dot_d32_small_sort_limit", DOT, SOFTMAX, DST, 2_500, 0, 32, 1, 0, 0, 1_024, 32, 64, 20, 2_300, 0.2),
     _case("dot_d32_above_small_sort", DOT, SOFTMAX, DST, 2_500, 0, 32, 1, 0, 0, 1_025, 32, 64, 20, 2_300, 0.2),
-    # one negative more than the single-sweep kernel holds (1024): d = 100 through the two-sweep kernel
+    # one negative more than sixteen tiles: a tile of one
     _case("dot_d100_n1025", DOT, SOFTMAX, DST, 6_000, 0, 100, 2, 0, 1, 300, 50, 1_025, 300, 700, 0.2),
     # margin-based ranking loss (pairwise hinge): about half of the pairs pay at these scales
     dict(_case("dot_d100_margin", DOT, MARGIN, DST, 8_000, 0, 100, 2, 0, 1, 600, 50, 300, 60, 1_300, 0.3), margin=1.0),
@@ -204,13 +204,13 @@ def test_wide_path_with_many_workgroups(c):
     _check_every_batch(c)
 
 
-@pytest.mark.parametrize("in_place", [True, False], ids=["reference_raised_in_place", "handed_to_two_sweep_kernel"])
-def test_single_sweep_kernel_out_of_range_chunks(monkeypatch, in_place):
-    """The single-sweep kernel takes the row maxima over its first tile of negatives (every T-th
+@pytest.mark.parametrize("in_place", [True, False], ids=["reference_raised_in_place", "handed_to_fp32_kernel"])
+def test_scores_beyond_the_reference_at_a_low_limit(monkeypatch, in_place):
+    """The kernel on bf16 parts takes the row maxima over its first tile of negatives (every T-th
     negative of the chunk, T = number of 64-negative tiles) as the softmax reference.  Where a
     score lies more than a limit above its row's reference, the reference is raised on the way
-    (numerators and accumulators rescaled), or (LEGEND_FAST_CHUNK_NO_RESCALE=1, and always for
-    scores that are not finite) the chunk is handed to the two-sweep kernel.  With the limit
+    (the wave's sums rescaled), or (LEGEND_FAST_CHUNK_NO_RESCALE=1, and always for
+    scores that are not finite) the chunk is handed to the fp32 kernel.  With the limit
     lowered to 1.25 the hot rows put some chunks of every batch on either path."""
     c, limit = _HOT_CASE, 1.25
     if not in_place:
@@ -275,15 +275,18 @@ def _beyond_reference(c, node, rel, edges, b, limit, epoch=1):
     return flags, np.array(margins)
 
 
-def _check_every_batch(c, beyond_limit=None):
+def _check_every_batch(c, beyond_limit=None, on_parts=None):
     """beyond_limit: also check, batch by batch, the library's count of workgroups that met a score beyond
-    their softmax reference by more than this limit against the prediction from the tables before the batch."""
+    their softmax reference by more than this limit against the prediction from the tables before the batch.
+    on_parts: also check whether the first batch ran on the kernel on bf16 parts (the launch over flagged workgroups follows that only)."""
     node, rel, edges = _inputs(c)
     L, ctx = _gpu_ctx(c, node, rel)
     try:
         i, j = c["i"], c["j"]
         for p in sorted({i, j}):
             L.legend_swap_partition(ctx, -1, p)
+        if on_parts is not None:
+            L.legend_profile_enable(ctx, 0xffffffff)
         run = OracleRun(_ocfg(c), node, rel if c["score"] else None)
         nb = -(-c["m"] // c["B"])
         before = _read_all(L, ctx, c)
@@ -296,6 +299,8 @@ def _check_every_batch(c, beyond_limit=None):
                 assert (np.abs(margins - beyond_limit) > 1e-2).all()        # no workgroup sits on the limit itself
                 L.legend_fallback_chunks_read(ctx)
             stats = L.legend_train_bucket_range(ctx, i, j, edges, epoch=1, batch_begin=b, batch_end=b + 1)
+            if on_parts is not None and b == 0:
+                assert L.legend_profile_read(ctx)["chunk_redo"]["launches"] == (1 if on_parts else 0)
             if beyond_limit is not None:
                 assert L.legend_fallback_chunks_read(ctx) == sum(flags), (b, sum(flags), len(flags))
                 seen.append((sum(flags), len(flags)))
@@ -331,15 +336,15 @@ _BEYOND_CASES = [
          hot_every=64, hot_scale=4.0),
     dict(_case("dot_d100_softmax_pos_hot_rows", DOT, SOFTMAX_POS, DST, 12_000, 0, 100, 2, 0, 1, 1_000, 50, 300, 0, 2_500, 1.05),
          hot_every=64, hot_scale=4.0),
-    # the single-sweep kernel's other dimension
+    # fewer dimensions
     dict(_case("distmult_d64_both_hot_rows", DISTMULT, SOFTMAX, BOTH, 12_000, 7, 64, 2, 0, 1, 1_000, 50, 300, 0, 2_500, 1.15),
          hot_every=64, hot_scale=4.0),
 ]
 
 
 @pytest.mark.parametrize("c", _BEYOND_CASES, ids=[c["name"] for c in _BEYOND_CASES])
-def test_single_sweep_kernel_scores_beyond_the_reference_at_the_real_limit(c):
-    """DistMult (both sides), ComplEx (all eight steps of negatives) and the Eq. 1 variant with the positive
+def test_scores_beyond_the_reference_at_the_real_limit(c):
+    """DistMult (both sides), ComplEx (sixteen tiles of negatives) and the Eq. 1 variant with the positive
     inside the log-sum-exp, with scores in the hundreds: in every batch some workgroups meet a score more than
     110 above the reference taken from their first tile of negatives and others do not (in the first batch and
     again later; never all of them); the library's count of them equals the prediction, and every batch matches
@@ -687,7 +692,7 @@ def _random_cases(seed, count, stds=(0.1, 0.3)):
     """Seeded random shapes: every score, loss and corruption mode over dimensions on both sides of the
     kernels' boundaries (multiples of 4 and not, 100, 128 | 132, 400), chunk sizes from 1 to two row tiles,
     negative counts around the tile size, diagonal and off-diagonal buckets.  stds: initial standard
-    deviations to draw from; 1 and above puts the scores in the tens to hundreds, where single-sweep
+    deviations to draw from; 1 and above puts the scores in the tens to hundreds, where
     chunks overrun their softmax reference and weights span the whole exponent range of fp32."""
     rng = np.random.default_rng(seed)
     cases = []

@@ -7,9 +7,9 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _run(monkeypatch, serial, calls, m, update_mode=0, no_small_update=False):
+def _run(monkeypatch, serial, calls, m, update_mode=0, no_small_update=False, d=20, N=33):
     from paper_2505_09258_amd import binding as L
-    V, d, B = 900, 20, 60
+    V, B = 900, 60
     rng = np.random.default_rng(3)
     node = (0.3 * rng.standard_normal((V, d))).astype(np.float32)
     rel = (0.3 * rng.standard_normal((4, d))).astype(np.float32)
@@ -17,7 +17,7 @@ def _run(monkeypatch, serial, calls, m, update_mode=0, no_small_update=False):
     monkeypatch.setenv("LEGEND_SERIAL_SORT", "1" if serial else "0")
     monkeypatch.setenv("LEGEND_NO_SMALL_UPDATE", "1" if no_small_update else "0")
     cfg = L.make_config(num_nodes=V, dim=d, num_partitions=2, num_relations=4, score=L.SCORE_DISTMULT, corrupt=L.CORRUPT_BOTH,
-                        batch_size=B, chunk_size=20, num_negs=33, num_degree_negs=5, seed=2, update_mode=update_mode)
+                        batch_size=B, chunk_size=20, num_negs=N, num_degree_negs=5, seed=2, update_mode=update_mode)
     ctx = L.legend_init_partitions(cfg, node, rel)
     try:
         for p in range(2):
@@ -39,6 +39,17 @@ def _run(monkeypatch, serial, calls, m, update_mode=0, no_small_update=False):
 def test_groups_give_the_bits_of_single_batches(monkeypatch, m, calls):
     a, ta = _run(monkeypatch, False, calls, m)
     b, tb = _run(monkeypatch, True, calls, m)
+    assert a == b
+    for x, y in zip(ta, tb):
+        assert (x == y).all()
+
+
+@pytest.mark.parametrize("m,calls", [(59, [(0, 1)]), (33 * 60 - 59, [(0, 33)] * 2), (80 * 60 - 11, [(3, 40), (40, 41), (10, 80)])])
+@pytest.mark.parametrize("d,N", [(36, 70), (100, 33)])
+def test_groups_on_the_kernel_on_bf16_parts(monkeypatch, m, calls, d, N):
+    """Its two launches a batch (more than 32 dimensions, 2500 negatives x dimensions and more) read their ids from a slab."""
+    a, ta = _run(monkeypatch, False, calls, m, d=d, N=N)
+    b, tb = _run(monkeypatch, True, calls, m, d=d, N=N)
     assert a == b
     for x, y in zip(ta, tb):
         assert (x == y).all()

@@ -13,9 +13,18 @@ pytestmark = pytest.mark.gpu
 # Dimensions on both sides of every class of column blocks (32, 64, 96, 100, 128), of slices of 32 and of the row alignments 16, 8 and 4;
 # negatives on both sides of tiles of 32 and 64 and beyond what LDS holds of their ids; rows on both sides of 16, 32 and 64.
 _EDGES = [
-    _case("dot_d1_n65_rows16", DOT, SOFTMAX, DST, 900, 0, 1, 1, 0, 0, 48, 16, 65, 0, 110, 0.5),
-    _case("dot_d31_n127_rows17", DOT, LOGISTIC, DST, 900, 0, 31, 1, 0, 0, 68, 17, 127, 0, 140, 0.4),
-    _case("distmult_d32_n128_rows32", DISTMULT, SOFTMAX, BOTH, 900, 3, 32, 1, 0, 0, 96, 32, 128, 9, 200, 0.4),
+    # up to 32 dimensions: the consumers share two blocks of columns by halves; every loss at every alignment
+    _case("dot_d1_n10000_rows16", DOT, SOFTMAX, DST, 900, 0, 1, 1, 0, 0, 32, 16, 10_000, 0, 70, 0.5),
+    _case("dot_d4_n1300_rows50", DOT, MARGIN, DST, 900, 0, 4, 1, 0, 0, 100, 50, 1_300, 0, 140, 0.5),
+    _case("dot_d17_n300_rows48", DOT, SOFTMAX_POS, DST, 900, 0, 17, 1, 0, 0, 96, 48, 300, 0, 200, 0.4),
+    _case("complex_d18_n300_rows40", COMPLEX, LOGISTIC, BOTH, 900, 3, 18, 1, 0, 0, 80, 40, 300, 0, 170, 0.4),
+    _case("complex_d26_n200_rows64", COMPLEX, SOFTMAX, SRC, 900, 3, 26, 2, 1, 0, 128, 64, 200, 0, 270, 0.4),
+    _case("dot_d29_n180_rows20", DOT, MARGIN, BOTH, 900, 0, 29, 1, 0, 0, 60, 20, 180, 0, 130, 0.4),
+    _case("distmult_d30_n200_rows33", DISTMULT, MARGIN, DST, 900, 3, 30, 1, 0, 0, 99, 33, 200, 0, 210, 0.4),
+    _case("dot_d31_n193_rows17", DOT, LOGISTIC, DST, 900, 0, 31, 1, 0, 0, 68, 17, 193, 0, 140, 0.4),
+    _case("distmult_d32_n257_rows32", DISTMULT, SOFTMAX, BOTH, 900, 3, 32, 1, 0, 0, 96, 32, 257, 9, 200, 0.4),
+    _case("dot_d32_n160_rows64", DOT, LOGISTIC, SRC, 900, 0, 32, 1, 0, 0, 128, 64, 160, 0, 270, 0.4),
+    # the other classes
     _case("complex_d34_n129_rows33", COMPLEX, MARGIN, SRC, 900, 3, 34, 2, 1, 0, 99, 33, 129, 0, 210, 0.4),
     _case("dot_d64_n193_rows64", DOT, SOFTMAX_POS, DST, 900, 0, 64, 1, 0, 0, 128, 64, 193, 0, 300, 0.3),
     _case("distmult_d65_n96_rows65", DISTMULT, LOGISTIC, BOTH, 900, 3, 65, 1, 0, 0, 130, 65, 96, 5, 270, 0.3),
@@ -27,20 +36,30 @@ _EDGES = [
     _case("dot_d101_n160_rows31", DOT, SOFTMAX_POS, BOTH, 900, 0, 101, 1, 0, 0, 93, 31, 160, 0, 200, 0.25),
     _case("complex_d126_n70_rows63", COMPLEX, SOFTMAX, SRC, 900, 3, 126, 1, 0, 0, 126, 63, 70, 0, 260, 0.25),
     _case("distmult_d128_n1100_rows48", DISTMULT, LOGISTIC, DST, 900, 3, 128, 1, 0, 0, 96, 48, 1100, 0, 200, 0.25),
-    # few negatives in a batch of many gradient rows: tiles that are empty or nearly so
-    _case("dot_d20_n1_many", DOT, SOFTMAX, DST, 2_000, 0, 20, 1, 0, 0, 2_100, 50, 1, 0, 2_200, 0.3),
-    _case("distmult_d100_n33_many", DISTMULT, SOFTMAX, BOTH, 2_000, 3, 100, 1, 0, 0, 1_600, 40, 33, 0, 1_700, 0.3),
+    # few negatives: tiles that are empty or nearly so
+    _case("dot_d128_n20_rows50", DOT, SOFTMAX, DST, 900, 0, 128, 1, 0, 0, 150, 50, 20, 0, 310, 0.25),
+    _case("distmult_d100_n33_rows40", DISTMULT, SOFTMAX, BOTH, 2_000, 3, 100, 1, 0, 0, 80, 40, 33, 0, 170, 0.3),
+    # more than 4096 gradient rows a batch
+    _case("distmult_d100_n100_many", DISTMULT, SOFTMAX, BOTH, 2_000, 3, 100, 1, 0, 0, 1_600, 40, 100, 0, 1_700, 0.3),
+    _case("dot_d20_n513_many", DOT, LOGISTIC, DST, 2_000, 0, 20, 1, 0, 0, 2_100, 50, 513, 0, 2_200, 0.3),
 ]
 
 
 @pytest.mark.parametrize("c", _EDGES, ids=[c["name"] for c in _EDGES])
 def test_at_the_edges_of_its_tiles(c):
-    _check_every_batch(c)
+    _check_every_batch(c, on_parts=True)
+
+
+@pytest.mark.parametrize("c", _EDGES, ids=[c["name"] for c in _EDGES])
+def test_the_same_through_the_fp32_kernel(monkeypatch, c):
+    """What serves atomic mode, small chunks and chunks with numbers that are not finite, at the same sizes."""
+    monkeypatch.setenv("LEGEND_NO_FAST_CHUNK", "1")
+    _check_every_batch(c, on_parts=False)
 
 
 @pytest.mark.parametrize("loss", [LOGISTIC, MARGIN], ids=["logistic", "margin"])
 @pytest.mark.parametrize("where", ["negative", "source", "huge_negative"])
-@pytest.mark.parametrize("d,C,N", [(20, 20, 70), (99, 64, 129), (128, 33, 200)])
+@pytest.mark.parametrize("d,C,N", [(20, 20, 250), (31, 50, 200), (99, 64, 129), (128, 33, 200)])
 def test_infinite_rows(loss, where, d, C, N):
     """One component that is infinite, or finite above the largest bfloat16, in a row of negatives or in a composed row: a gradient
     sum is infinite, or not a number, exactly where the sum in 64 bits of the same numbers is beyond fp32, or not a number."""
@@ -55,7 +74,7 @@ def test_infinite_rows(loss, where, d, C, N):
     else:
         row = next(int(v) for v in neg[0] if v >= 400)
     node[row, d // 3] = 3.4e38 if where == "huge_negative" else np.inf
-    state, _ = _one_batch(node, None, edges, score=DOT, loss=loss, corrupt=DST, **kw)
+    state, _ = _one_batch(node, None, edges, score=DOT, loss=loss, corrupt=DST, on_parts=True, **kw)
     g = _expected(node, edges, loss=loss, **kw)
     with np.errstate(all="ignore"):
         want = (g.astype(np.float32) * g.astype(np.float32))

@@ -9,8 +9,9 @@ pytestmark = pytest.mark.gpu
 DOT, DISTMULT, COMPLEX, TRANSE = 0, 1, 2, 3
 
 
-def _tables(monkeypatch, knob, score, d, B, C, N):
+def _tables(monkeypatch, knob, score, d, B, C, N, fp32=False):
     from paper_2505_09258_amd import binding as L
+    monkeypatch.setenv("LEGEND_NO_FAST_CHUNK", "1" if fp32 else "0")
     if knob is None:
         monkeypatch.delenv("LEGEND_STREAM_ROWS", raising=False)
     else:
@@ -31,12 +32,21 @@ def _tables(monkeypatch, knob, score, d, B, C, N):
         L.legend_destroy(ctx)
 
 
-# single-sweep kernel, two-sweep kernel (rows of 16, 8 and 4 bytes' alignment), translational, wide path; a small batch
+# kernel on bf16 parts (which marks none of its stores; rows of 16, 8 and 4 bytes' alignment), translational, wide path; a small batch
 @pytest.mark.parametrize("score,d,B,C,N", [(DOT, 100, 500, 50, 200), (COMPLEX, 64, 500, 50, 200), (DOT, 128, 300, 50, 300),
                                            (DISTMULT, 50, 600, 60, 100), (DOT, 33, 600, 60, 100), (TRANSE, 60, 600, 60, 100),
                                            (TRANSE, 31, 600, 60, 100), (DISTMULT, 150, 300, 60, 200), (DOT, 256, 300, 60, 200),
                                            (DISTMULT, 32, 200, 50, 30)])
 def test_same_bits(monkeypatch, score, d, B, C, N):
     always, never, chosen = (_tables(monkeypatch, k, score, d, B, C, N) for k in ("1", "0", None))
+    for x, y, z in zip(always, never, chosen):
+        assert np.array_equal(x, y) and np.array_equal(x, z)
+
+
+# fp32 kernel, rows of 16 (with the dimension folded in and without), 8 and 4 bytes' alignment
+@pytest.mark.parametrize("score,d,B,C,N", [(DOT, 100, 500, 50, 200), (DOT, 128, 300, 50, 300), (COMPLEX, 64, 500, 50, 200),
+                                           (DISTMULT, 50, 600, 60, 100), (DOT, 33, 600, 60, 100)])
+def test_same_bits_from_the_fp32_kernel(monkeypatch, score, d, B, C, N):
+    always, never, chosen = (_tables(monkeypatch, k, score, d, B, C, N, fp32=True) for k in ("1", "0", None))
     for x, y, z in zip(always, never, chosen):
         assert np.array_equal(x, y) and np.array_equal(x, z)
