@@ -18,8 +18,8 @@
 // time; memory is read twice, 1.1 GB.  That batch takes 0.49 ms by itself, 0.54 with
 // fp32 instructions and a single sweep; both sides and complex products 0.98 (1.29).  Against the two-sweep kernel on fp32 instructions:
 // d = 50, both sides, chunks of 100, 0.56 ms (0.95); logistic at d = 128, 20 011 edges, 333 negatives, 0.131 ms (0.24).
-// Against 64 bits the gradients are closer than with fp32 instructions (2-norm over one batch, 14 shapes of d = 8 to 128 and all four losses,
-// three seeds each: geometric mean 6.7e-8, 8.1e-8 before; 39 of 42 smaller, the others at scores in the tens).
+// Against 64 bits the gradients are closer than with fp32 instructions in each of 19 shapes (2-norm over one batch, source rows and the
+// others apart; d = 64 to 128, softmax, logistic and margin losses, scores from 0.1 to beyond 100, eight seeds each).
 //
 // Tried: the operand of the scores loaded by neighbouring lanes and exchanged between lanes in registers (216 more vector instructions a
 // tile, no faster); the gradient rows staged in LDS with three barriers a step (0.48 ms, but d = 50 0.67); the consumers bringing the
