@@ -421,13 +421,18 @@ int stage_edges(legend_ctx* c, int i, int j, const int32_t* edges, int64_t m, in
 // by total: d = 100, 99 to 214 MB 1 to 4 % more, 252 MB 1 % more, 290 MB 1 % less, 443 MB (1M rows of tables and more: 1.2 GB) 2 %
 // (3 %) less; d = 64, 208 MB 1 % more, 256 MB 4 % less, 354 MB 6 % less; d = 50 (200-byte rows), 56 MB 4 % and 182 MB
 // 5 % more, 269 MB 1 % less; wide path d = 400, 158 MB 1 % more, 267 MB 2 %, 320 MB 4 %, 480 MB 8 % less.
-// (Figures with k_chunk's marked stores; k_chunk_split never marks its stores, which are pieces of lines, so there the update's loads alone.)
-int32_t streams_rows(const legend_ctx* c, int i, int j, int64_t m) {
-    constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+// Those are figures with k_chunk's marked stores.  k_chunk_split never marks its stores, which are pieces of lines; the marks of the update's loads
+// alone pay only where the rows themselves take more than 150 MB, whatever the tables.  By rows (total): d = 100, 84 MB (99 to 389) 2 to 9 % more,
+// 126 MB (278, 431, 736) 1 % more, 1 % more, 1 % less, 168 MB (320 to 778) 1 % less, 252 MB 2 % less, 336 MB 2 to 3 % less; d = 128, 117 MB (264) 1 % more,
+// 161 MB (308, 649) 0.5 % less, 215 MB 2 % less, 322 MB 2 to 5 % less; d = 50, 105 MB (296) 3 % more, 126 MB (278, 584) 3 and 1 % more, 189 and 210 MB 0
+// to 1 % more.
+int32_t streams_rows(const legend_ctx* c, const BucketParams& bp, int i, int j, int64_t m) {
+    constexpr int64_t kCacheBytes = (int64_t)256 << 20, kSplitRowBytes = (int64_t)150 << 20;
     const BatchGeom g = make_geom(c, (int)std::min<int64_t>(m, c->cfg.batch_size));
     const int64_t table_rows = rows_valid(c, i) + (i != j ? rows_valid(c, j) : 0) + (c->uses_rel ? c->nrel_rows : 0);
     int64_t floats = (g.n_occ + 2 * table_rows) * c->d;                        // embeddings and states
     if (c->d > 128) floats += (int64_t)g.sides * g.P * (2 * c->d + gemm_npad(g.N));       // Q, its gradient, scores
+    if (chunks_use_split(g, bp, c->ws) && g.n_occ * c->d * (int64_t)sizeof(float) <= kSplitRowBytes) return 0;
     return floats * (int64_t)sizeof(float) > kCacheBytes;
 }
 
@@ -460,7 +465,7 @@ int bucket_params(legend_ctx* c, int i, int j, const int32_t* dev_edges, int64_t
     p.key_base_dst = i == j ? 0u : (uint32_t)c->Rp;
     p.key_base_rel = i == j ? (uint32_t)c->Rp : (uint32_t)(2 * c->Rp);
     p.num_degree_negs = c->cfg.num_degree_negs;
-    p.stream_rows = c->stream_rows >= 0 ? c->stream_rows : streams_rows(c, i, j, m);
+    p.stream_rows = c->stream_rows >= 0 ? c->stream_rows : streams_rows(c, p, i, j, m);
     p.lr = c->cfg.lr;
     p.eps = c->cfg.eps;
     p.neg_weight = c->cfg.neg_weight >= 0.f ? c->cfg.neg_weight : 1.0f / (float)c->cfg.num_negs;
