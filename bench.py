@@ -613,7 +613,7 @@ def main() -> int:
         "roofline": res["roofline"], "update": res["update"], "kernels": res["kernels"],
         # workgroups (of K x 1000 x sides) whose softmax reference was raised on the way: a tuning aid
         "raised_reference_workgroups": res["fallback_chunks"],
-        "update_mode_note": "deterministic is the fast mode: the atomic mode measures 2.1e7 edges/s on c2 against 5.5e7 "
+        "update_mode_note": "deterministic is the fast mode: the atomic mode measures 2.1e7 edges/s on c2 against 5.4e7 "
                             "(1.1e8 fp32 atomics per batch cost 1.3 ms, profiles/c2_atomic_kernel_trace.txt)",
     }
     if "cpu_baseline" in res:

@@ -15,8 +15,8 @@
 //
 // What bounds it: issue and latency at two waves a SIMD (a wave issues one vector instruction per five cycles; the producers' chain sets the
 // pace of sweep 2).  The matrix pipe needs 130 us of a batch of 50 000 edges, 1000 negatives, d = 100, and is busy a quarter of the
-// time; memory is read twice, 1.1 GB.  That batch takes 0.49 ms by itself, 0.54 with
-// fp32 instructions and a single sweep; both sides and complex products 0.98 (1.29).  Against the two-sweep kernel on fp32 instructions:
+// time; memory is read twice, 1.1 GB.  That batch takes 0.48 ms by itself (0.52 while the sums of G_Q spilled), 0.53 with
+// fp32 instructions and a single sweep; both sides and complex products 0.94 (1.21).  Against the two-sweep kernel on fp32 instructions:
 // d = 50, both sides, chunks of 100, 0.56 ms (0.95); logistic at d = 128, 20 011 edges, 333 negatives, 0.131 ms (0.24).
 // Against 64 bits the gradients are closer than with fp32 instructions in each of 19 shapes (2-norm over one batch, source rows and the
 // others apart; d = 64 to 128, softmax, logistic and margin losses, scores from 0.1 to beyond 100, eight seeds each).
