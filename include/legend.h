@@ -308,8 +308,8 @@ int legend_unique_rows_read(legend_ctx* ctx, int64_t* unique_rows, int64_t* batc
 
 /* Workgroups (one row tile of one chunk) of the batch kernel on bf16 parts (product scores,
  * dim <= 128, softmax losses) that met a score too far above their softmax reference (the
- * reference is then raised on the way) or a number that is not finite (the chunk is then
- * handed over to the fp32 kernel) since the last call, then cleared.  A tuning aid: 0 early
+ * reference is then raised on the way), a number that is not finite or a row without a score
+ * above -1e30 (the chunk is then handed over to the fp32 kernel) since the last call, then cleared.  A tuning aid: 0 early
  * in training. */
 int legend_fallback_chunks_read(legend_ctx* ctx, int64_t* chunks);
 
